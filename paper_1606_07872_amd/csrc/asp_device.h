@@ -117,23 +117,26 @@ struct DevState {
 };
 constexpr int kSqSlots = 4096;
 
-// State of one fit shared by the work-groups of the fit kernel.  The
-// published part (m .. th_old) is written by one work-group and read by all
-// after the generation counter moves; the LM part is touched only by the
-// work-group that reduces a trial.
 constexpr int kNOutMax = (kMaxN + 1) * (kMaxN + 2) / 2;       // augmented Gram entries
 constexpr int kPartStride = kNOutMax + 3;                      // + F, chi2 (FP64), pixels
 constexpr int kMaxGroups = 64;     // partial rows beyond the grid, one per arrival group
 
+// What the work-groups of one fit (or of one batch team) share.  The leader's
+// messages are words of (sequence number << 32 | 32 bits of payload), each
+// written by one 64-bit store: a reader that finds one sequence number in all
+// the words it needs has the whole message, in one round trip and without a
+// fence.  mail: m | command << 5 | evaluating work-groups << 8, the fit's
+// number, the field, the epoch of R, then the point under evaluation as pairs
+// of 32-bit halves; old: the old members' stored parameters, tagged with the
+// fit's number.  Counters that many work-groups advance have a line each.
+constexpr int kMailHead = 4;
+struct alignas(128) Counter { unsigned int n, pad[31]; };
 struct FitGlobal {
-    int32_t m, n, done, cmd;            // cmd, field: the batched kernel's command
-    int32_t field, pad0;
-    double th_e[kMaxN];                 // parameters under evaluation
-    double th_old[kMaxN];               // stored parameters of the old members
-    unsigned int gen;                   // publication counter
-    unsigned int beat;                  // the batched leader's iteration heartbeat
-    unsigned int top;                   // second-level arrivals (one per group)
-    unsigned int arrive_g[kMaxGroups];  // first-level arrivals (one per work-group)
+    alignas(128) unsigned long long mail[kMailHead + 2 * kMaxN];
+    alignas(128) unsigned long long old[2 * kMaxN];
+    Counter beat;                       // the batched leader's iteration heartbeat
+    Counter top;                        // check-in; second-level arrivals (one per group)
+    Counter arrive_g[kMaxGroups];       // first-level arrivals (one per work-group)
 };
 
 // The smoothing method's kernels: trial widths, taps and the device copy of

@@ -18,11 +18,23 @@
 // FP32 for the augmented Gram matrix [J r]^T [J r], summed per tile and
 // Kahan-compensated across tiles, while F and chi2 stay FP64.
 //
-// Every work-group arrives once per round: at its group's counter (kGroup
-// work-groups), the last of a group sums the group's partial rows in order and
-// arrives at the top counter; work-group 0 waits for all groups, so no
-// work-group can fall a round behind.  Every wait is bounded; a wait that runs
-// out marks the context with ASP_ERR_DEVICE and every work-group leaves.
+// The work-groups with tiles of a trial arrive at their group's counter (kGroup
+// work-groups); work-group 0 waits for all of them before it publishes again.
+// Up to eight parameters it sums their partial rows itself; above, the last
+// of a group sums the group's rows in order and arrives at the top counter.
+// Work-groups without tiles of a trial only take note of it.  Every wait is
+// bounded; a wait that runs out marks the context with ASP_ERR_DEVICE and
+// every work-group leaves.
+//
+// A trial is a chain of latencies, not of work: 54 k pixels on 105
+// work-groups take about 2 us of arithmetic.  So the data that cross between
+// work-groups inside a fit (the trial point, the partial rows) go through
+// agent-scope atomic stores and loads, which write through and read the
+// coherent copy, and a store is known to be there when its wave's vmcnt is
+// zero.  No release or acquire of a whole cache is then needed per trial
+// (measured for one publication and one arrival of 256 work-groups: 1.64 us
+// against 3.58 us with releases), and a message is read in one round trip
+// (FitGlobal::mail).
 #include <math.h>
 
 #include "asp_device.h"
@@ -35,6 +47,10 @@ constexpr int kOwnMax = (kNOutMax + kT - 1) / kT;
 constexpr size_t kTileBytes = sizeof(float) * kT * kTileStride;
 constexpr size_t kMatBytes = sizeof(double) * kMaxN * kMaxN;
 constexpr size_t kFitLds = kTileBytes + 2 * kMatBytes;   // tile (or A) | two Gram buffers
+// The work-group's own partial row, at the end of the tile buffer: it is
+// written when the tile is no longer read.
+constexpr size_t kRowOffset = kTileBytes - sizeof(double) * kPartStride;
+static_assert(kRowOffset % sizeof(double) == 0, "row alignment");
 constexpr int kGroup = 16;        // work-groups per first-level arrival group
 static_assert(kTileBytes >= kMatBytes, "A shares the tile buffer");
 static_assert(kTileBytes >= sizeof(float) * kUpdTabFloats, "the update's tables share the tile buffer");
@@ -58,12 +74,18 @@ struct WGShared {
     double ox[kMaxM], oy[kMaxM], oamp[kMaxM], oinv2[kMaxM];
     int32_t m, n;
     double wsum[4][3];
+    unsigned long long prof[kProfSlots];   // phase timers and counts of this fit (leader)
+    unsigned long long eval_px, gram_flops;   // of this fit's trials (thread 0 of the leader)
     double wred[kT / 64][48];
     // the reduced trial (work-group 0)
     double ge[kMaxN], Fe, chi2e;
     int64_t npx_e;
     // LM state (work-group 0)
-    double th_c[kMaxN], th_e[kMaxN], g_c[kMaxN], lo[kMaxN], hi[kMaxN], th0[kMaxN], th_old[kMaxN];
+    double th_c[kMaxN], g_c[kMaxN], lo[kMaxN], hi[kMaxN], th0[kMaxN];
+    // the trial point and the old members' stored parameters; the other
+    // work-groups receive them as 32-bit halves
+    union { double th_e[kMaxN]; uint32_t th_e32[2 * kMaxN]; };
+    union { double th_old[kMaxN]; uint32_t th_old32[2 * kMaxN]; };
     double dd[kMaxN], rhs[kMaxN], rhs_copy[kMaxN], delta[kMaxN];
     double ldiag[kMaxN];           // L_kk of the work-group Cholesky
     int32_t frozen[kMaxN];
@@ -84,10 +106,15 @@ struct WGShared {
     // batched fields (leader and followers)
     int32_t cmd, fld, go;
     int64_t k_target, upx;
+    // messages (the other work-groups: the last one read)
+    unsigned int gen;              // sequence number
+    unsigned int fit_no;           // leader: the fit's number, 0 before its first trial
+    unsigned int fit_have;         // others: the fit whose th_old is held
+    unsigned int epoch, epoch_have;   // of R (batched fields)
+    int32_t geff, poll_n;
     // control
     unsigned long long tmark;      // phase timer mark (thread 0)
     unsigned long long tfit;       // start of the fit (thread 0)
-    unsigned int gen;
     int32_t last, abort, done, ok, finished, accept, stop;
     int32_t upd;                   // the fit committed and this launch also updates R
 };
@@ -99,88 +126,239 @@ __device__ inline void mark(WGShared &S)
     if (threadIdx.x == 0) S.tmark = now_ticks();
 }
 
-__device__ __forceinline__ void lap(const Params &p, WGShared &S, int slot)
+__device__ __forceinline__ void lap(WGShared &S, int slot)
 {
     if (threadIdx.x == 0) {
         const unsigned long long now = now_ticks();
-        atomicAdd(&p.st->prof[slot], now - S.tmark);
+        S.prof[slot] += now - S.tmark;
         S.tmark = now;
     }
 }
 
+// The timers and counts of this fit into the device state; they start again
+// from zero.  Thread 0 keeps them in LDS meanwhile: a read-modify-write of the
+// device state per trial would put a memory round trip on the LM chain.
+__device__ __forceinline__ void flush_counts(const Params &p, WGShared &S)
+{
+    if (threadIdx.x != 0) return;
+    DevState *st = p.st;
+    for (int i = 0; i < kProfSlots; ++i) {
+        st->prof[i] += S.prof[i];
+        S.prof[i] = 0ull;
+    }
+    st->sum_eval_px += S.eval_px;
+    st->sum_gram_flops += S.gram_flops;
+    S.eval_px = S.gram_flops = 0ull;
+}
+
 // ---------------------------------------------------------------------------
 // Synchronisation between work-groups.  Polling is relaxed (no cache
-// maintenance per poll); the fence after it is the acquire.  A work-group
-// signals after a barrier, by one release operation of thread 0.
+// maintenance per poll).  Data written with ordinary stores (the residual, the
+// update's plan) cross by a release and an acquire at agent scope; trial points
+// and partial rows cross by atomic stores and loads.
 // ---------------------------------------------------------------------------
 
 __device__ inline void acquire_fence() { __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent"); }
 
-// Loads of data another work-group published: agent-scope atomic loads read
-// the coherent copy, so a reader that only needs such data can skip the
-// acquire fence (which would also drop the read-only residual from its L2).
-__device__ inline double ld_shared(const double *q)
+// Loads and stores of data that cross between work-groups at agent scope: they
+// read and write the coherent copy.
+template <typename T>
+__device__ inline T ld_shared(const T *q)
 {
     return __hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ inline int32_t ld_shared(const int32_t *q)
+template <typename T>
+__device__ inline void st_shared(T *q, T v)
 {
-    return __hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(q, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// Every store of this wave has reached the scope it was made at.
+__device__ inline void wave_stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+enum { kCmdPeak = 1, kCmdEval = 2, kCmdUpdate = 3, kCmdExit = 4 };
+
+// The leader's next message (the whole work-group calls it): a command, and
+// with kCmdEval the trial point S.th_e for geff work-groups, with the old
+// members' stored parameters before the first trial of a fit.  release: plain
+// stores of this work-group go before it.
+__device__ __forceinline__ void publish(FitGlobal *G, WGShared &S, int cmd, int geff = 0,
+                                        int field = 0, bool release = false)
+{
+    static_assert(kMaxM < 32 && kCmdExit < 8 && kMaxGroups * kGroup < (1 << 24), "header bits");
+    if (release) wave_stores_done();
+    __syncthreads();
+    const int t = threadIdx.x;
+    if (t >= 64) return;
+    // the counters reset after the last trial are in place before this message
+    wave_stores_done();
+    if (release) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+    const unsigned int gen = S.gen + 1u;
+    const bool first = cmd == kCmdEval && S.fit_no == 0u;
+    const unsigned int fit_no = first ? gen : S.fit_no;
+    const unsigned long long tag = (unsigned long long)gen << 32;
+    const int nw = cmd == kCmdEval ? 2 * S.n : 0;
+    if (first)
+        for (int w = 8 + t; w < nw; w += 64)
+            st_shared(&G->old[w], ((unsigned long long)fit_no << 32) | S.th_old32[w]);
+    for (int w = t; w < kMailHead + nw; w += 64) {
+        uint32_t v;
+        if (w == 0) v = (nw ? (uint32_t)S.m : 0u) | ((uint32_t)cmd << 5) | ((uint32_t)geff << 8);
+        else if (w == 1) v = fit_no;
+        else if (w == 2) v = (uint32_t)field;
+        else if (w == 3) v = S.epoch;
+        else v = S.th_e32[w - kMailHead];
+        st_shared(&G->mail[w], tag | v);
+    }
+    if (t == 0) {
+        S.gen = gen;
+        if (first) S.fit_no = fit_no;
+    }
 }
 
-// Every wait is bounded in time: `limit` device wall-clock ticks.  With
-// `beat`, the bound restarts whenever the heartbeat moves: a leader that
-// works alone for a long time (small fields of a batch) keeps its followers
-// waiting without letting them time out.
-__device__ __forceinline__ bool wait_publish(FitGlobal *G, WGShared &S, unsigned long long limit,
-                                             bool acquire = true, bool beat = false)
+// The next message, into S (command, geff, field, epoch and, for a trial in
+// which work-group `wg` has tiles, m, n, th_e and th_old).  Wave 0 polls the
+// words the last one had.  A work-group without tiles may find that the
+// leader has moved on; one with tiles cannot, as the leader waits for it.
+// Bounded in time: `limit` device wall-clock ticks.  With `beat`, the bound
+// restarts whenever the heartbeat moves: a leader that works alone for a long
+// time (small fields of a batch) keeps its followers waiting without letting
+// them time out.
+__device__ __forceinline__ bool wait_mail(FitGlobal *G, WGShared &S, int wg,
+                                          unsigned long long limit, bool beat = false)
 {
-    if (threadIdx.x == 0) {
-        unsigned int now = S.gen;
-        unsigned int last_beat = beat ? __hip_atomic_load(&G->beat, __ATOMIC_RELAXED,
-                                                          __HIP_MEMORY_SCOPE_AGENT) : 0u;
+    const int t = threadIdx.x;
+    if (t < 64) {
+        const unsigned int seen = S.gen;
+        int nw = S.poll_n;
+        unsigned int last_beat = beat ? ld_shared(&G->beat.n) : 0u;
         unsigned long long t0 = now_ticks();
+        unsigned long long w = 0ull;
+        unsigned int gen = seen;
+        uint32_t head = 0;
+        int need = 0;
+        bool ok = false;
         for (;;) {
-            now = __hip_atomic_load(&G->gen, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (now != S.gen) break;
+            w = t < nw ? ld_shared(&G->mail[t]) : 0ull;
+            gen = (unsigned int)__builtin_amdgcn_readfirstlane((int)(w >> 32));
+            if (gen != seen) {
+                head = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)w);
+                const bool mine = ((head >> 5) & 7u) == kCmdEval && wg < (int)(head >> 8);
+                need = kMailHead + (mine ? 8 * (int)(head & 31u) : 0);
+                const int want = need < 64 ? need : 64;
+                if (nw >= want && __all(t >= want || (unsigned int)(w >> 32) == gen)) {
+                    ok = true;
+                    break;
+                }
+                if (nw < want) nw = want;
+            }
             const unsigned long long tn = now_ticks();
             if (beat) {
-                const unsigned int b = __hip_atomic_load(&G->beat, __ATOMIC_RELAXED,
-                                                         __HIP_MEMORY_SCOPE_AGENT);
+                const unsigned int b = ld_shared(&G->beat.n);
                 if (b != last_beat) { last_beat = b; t0 = tn; }
             }
             if (tn - t0 > limit) break;
-            __builtin_amdgcn_s_sleep(kPollSleep);
+            if (gen == seen) __builtin_amdgcn_s_sleep(kPollSleep);
         }
-        S.abort = (now == S.gen) ? 1 : 0;
-        S.gen = now;
-        if (acquire) acquire_fence();
+        if (ok) {
+            const bool mine = need > kMailHead;
+            if (t >= kMailHead && t < need) S.th_e32[t - kMailHead] = (uint32_t)w;
+            for (int b = 64; b < need && ok; b += 64) {
+                unsigned long long x = 0ull;
+                for (;;) {
+                    x = b + t < need ? ld_shared(&G->mail[b + t]) : 0ull;
+                    if (__all(b + t >= need || (unsigned int)(x >> 32) == gen)) break;
+                    if (now_ticks() - t0 > limit) { ok = false; break; }
+                }
+                if (b + t < need) S.th_e32[b + t - kMailHead] = (uint32_t)x;
+            }
+            const unsigned int fit_no = (unsigned int)__builtin_amdgcn_readlane((int)(uint32_t)w, 1);
+            const int no = 8 * (int)(head & 31u);
+            if (mine && fit_no != S.fit_have) {
+                for (int b = 0; b < no && ok; b += 64) {
+                    const int i = b + t;
+                    const bool want = i >= 8 && i < no;
+                    unsigned long long x = 0ull;
+                    for (;;) {
+                        x = want ? ld_shared(&G->old[i]) : 0ull;
+                        if (__all(!want || (unsigned int)(x >> 32) == fit_no)) break;
+                        if (now_ticks() - t0 > limit) { ok = false; break; }
+                    }
+                    if (want) S.th_old32[i] = (uint32_t)x;
+                }
+                if (t == 0) S.fit_have = fit_no;
+            }
+            const int field = __builtin_amdgcn_readlane((int)(uint32_t)w, 2);
+            const unsigned int epoch = (unsigned int)__builtin_amdgcn_readlane((int)(uint32_t)w, 3);
+            if (t == 0) {
+                S.cmd = (int32_t)((head >> 5) & 7u);
+                S.geff = (int32_t)(head >> 8);
+                S.fld = field;
+                S.epoch = epoch;
+                if (mine) {
+                    S.m = (int32_t)(head & 31u);
+                    S.n = 4 * S.m;
+                    S.poll_n = need < 64 ? need : 64;
+                }
+            }
+        }
+        if (t == 0) {
+            S.gen = gen;
+            S.abort = ok ? 0 : 1;
+        }
     }
     __syncthreads();
     return S.abort == 0;
 }
 
-// The barrier makes every thread's stores visible to thread 0, whose release
-// at agent scope then covers them (the pattern of a grid-wide barrier).
-__device__ __forceinline__ void publish(FitGlobal *G)
+// Before the first message of a launch: the number of the last one, and
+// nothing held (thread 0; a barrier follows).
+__device__ __forceinline__ void mail_begin(FitGlobal *G, WGShared &S)
 {
-    __syncthreads();
-    if (threadIdx.x == 0)
-        __hip_atomic_fetch_add(&G->gen, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+    S.gen = (unsigned int)(ld_shared(&G->mail[0]) >> 32);
+    S.fit_no = 0u;
+    S.fit_have = 0u;
+    S.epoch = S.epoch_have = 0u;
+    S.poll_n = kMailHead + 8;
+    S.abort = 0;
+    for (int i = 0; i < kProfSlots; ++i) S.prof[i] = 0ull;
+    S.eval_px = S.gram_flops = 0ull;
 }
 
 // Thread 0 waits until *ctr reaches target; returns false on timeout.
 __device__ __forceinline__ bool spin_until(unsigned int *ctr, unsigned int target,
-                                           unsigned long long limit, bool acquire = true)
+                                           unsigned long long limit)
 {
     const unsigned long long t0 = now_ticks();
-    bool ok = true;
-    while (__hip_atomic_load(ctr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
-        if (now_ticks() - t0 > limit) { ok = false; break; }
+    while (ld_shared(ctr) < target) {
+        if (now_ticks() - t0 > limit) return false;
         __builtin_amdgcn_s_sleep(kPollSleep);
     }
-    if (acquire) acquire_fence();
-    return ok;
+    return true;
+}
+
+// The leader waits until work-groups 1 .. count-1 have each arrived once at the
+// counter of their group of gs, then clears the counters: lane g of wave 0
+// polls group g's.  Bounded in time.
+__device__ __forceinline__ bool wait_groups(FitGlobal *G, WGShared &S, int count, int gs,
+                                            unsigned long long limit)
+{
+    const int t = threadIdx.x;
+    if (t < 64) {
+        const int lo = t * gs, hi = lo + gs < count ? lo + gs : count;
+        const int need = hi - lo - (t == 0 ? 1 : 0);
+        const bool live = need > 0;
+        const unsigned long long t0 = now_ticks();
+        bool ok = true;
+        for (;;) {
+            const unsigned int v = live ? ld_shared(&G->arrive_g[t].n) : 0u;
+            if (__all(!live || (int)v >= need)) break;
+            if (now_ticks() - t0 > limit) { ok = false; break; }
+        }
+        if (live) st_shared(&G->arrive_g[t].n, 0u);
+        if (t == 0) S.abort = ok ? 0 : 1;
+    }
+    __syncthreads();
+    return S.abort == 0;
 }
 
 // ---------------------------------------------------------------------------
@@ -219,9 +397,9 @@ __device__ __forceinline__ void consider(const Params &p, WGShared &S, int64_t j
     if (S.nch >= p.max_active - 1) S.sel_done = 1;
 }
 
-// Start values, active set, bounds; the start point goes to S.th_e and is
-// published in G.  Work-group 0, whole work-group.
-__device__ __forceinline__ void setup_fit(const Params &p, FitGlobal *G, WGShared &S, bool use_prop)
+// Start values, active set, bounds; the start point goes to S.th_e.
+// Work-group 0, whole work-group.
+__device__ __forceinline__ void setup_fit(const Params &p, WGShared &S, bool use_prop)
 {
     const int t = threadIdx.x;
     const double omega_b = p.st->omega_b;
@@ -320,8 +498,7 @@ __device__ __forceinline__ void setup_fit(const Params &p, FitGlobal *G, WGShare
         S.phase = 0;
         S.trials = 0;
         S.converged = 0;
-        G->m = m;
-        G->n = 4 * m;
+        S.fit_no = 0u;                 // the next message opens a fit
     }
     __syncthreads();
     if (t < m) {
@@ -358,8 +535,6 @@ __device__ __forceinline__ void setup_fit(const Params &p, FitGlobal *G, WGShare
             if (!(v >= lo4[q])) v = lo4[q];
             if (v > hi4[q]) v = hi4[q];
             S.th_e[i] = v;
-            G->th_e[i] = v;
-            G->th_old[i] = S.th_old[i];
         }
     }
     __syncthreads();
@@ -379,48 +554,6 @@ __device__ inline void out_pair(int o, int n, int &i, int &k)
     k = r + (o - start);
 }
 
-// Member constants at theta (th_e) and the old members' stored Gaussians
-// (th_old), from the published copy or from work-group 0's own.
-__device__ __forceinline__ void prepare(const Params &p, WGShared &S, int m, const double *th_e,
-                                        const double *th_old, bool published = false)
-{
-    const int t = threadIdx.x;
-    __syncthreads();
-    if (t == 0) { S.m = m; S.n = 4 * m; }
-    __syncthreads();
-    if (t < S.m) {
-        // published: another work-group's copy in global memory
-        auto ld = [&](const double *q) { return published ? ld_shared(q) : *q; };
-        const double a = ld(th_e + 4 * t), x = ld(th_e + 4 * t + 1), y = ld(th_e + 4 * t + 2),
-                     s = ld(th_e + 4 * t + 3);
-        make_window(x, y, halfwidth(s, p.window_sigmas), p.H, p.W, S.win[t]);
-        const double s2 = s * s;
-        S.mx[t] = x;
-        S.my[t] = y;
-        S.mamp[t] = a;
-        S.minv2[t] = 1.0 / (2.0 * s2);
-        S.minvs2[t] = 1.0 / s2;
-        S.minvs3[t] = 1.0 / (s2 * s);
-        if (t > 0) {
-            const double oa = ld(th_old + 4 * t), ox = ld(th_old + 4 * t + 1),
-                         oy = ld(th_old + 4 * t + 2), os = ld(th_old + 4 * t + 3);
-            make_window(ox, oy, halfwidth(os, p.window_sigmas), p.H, p.W, S.wold[t]);
-            S.ox[t] = ox;
-            S.oy[t] = oy;
-            S.oamp[t] = oa;
-            S.oinv2[t] = 1.0 / (2.0 * os * os);
-        }
-    }
-    __syncthreads();
-    if (t == 0) {
-        S.pref[0] = 0;
-        for (int j = 0; j < S.m; ++j)
-            S.pref[j + 1] = S.pref[j] + (int64_t)(S.win[j][1] - S.win[j][0] + 1) *
-                                            (S.win[j][3] - S.win[j][2] + 1);
-    }
-    __syncthreads();
-}
-
 // Orders the LDS accesses of one wave: the lanes of a wave issue LDS
 // instructions together and the LDS serves them in program order, so after
 // this point every lane sees what any lane of the wave wrote before it; the
@@ -430,6 +563,49 @@ __device__ __forceinline__ void wave_lds_sync()
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Member constants at S.th_e, the old members' stored Gaussians at S.th_old
+// and the windows' pixel counts, by the first lanes of wave 0.  A barrier
+// lies between the writes of th_e and this call.
+__device__ __forceinline__ void prepare(const Params &p, WGShared &S)
+{
+    const int t = threadIdx.x;
+    if (t < 64) {
+        const int m = S.m;
+        int64_t area = 0;
+        if (t < m) {
+            const double a = S.th_e[4 * t], x = S.th_e[4 * t + 1], y = S.th_e[4 * t + 2],
+                         s = S.th_e[4 * t + 3];
+            int32_t w[4];
+            make_window(x, y, halfwidth(s, p.window_sigmas), p.H, p.W, w);
+            for (int q = 0; q < 4; ++q) S.win[t][q] = w[q];
+            area = (int64_t)(w[1] - w[0] + 1) * (w[3] - w[2] + 1);
+            const double s2 = s * s;
+            S.mx[t] = x;
+            S.my[t] = y;
+            S.mamp[t] = a;
+            S.minv2[t] = 1.0 / (2.0 * s2);
+            S.minvs2[t] = 1.0 / s2;
+            S.minvs3[t] = 1.0 / (s2 * s);
+            if (t > 0) {
+                const double ox = S.th_old[4 * t + 1], oy = S.th_old[4 * t + 2],
+                             os = S.th_old[4 * t + 3];
+                make_window(ox, oy, halfwidth(os, p.window_sigmas), p.H, p.W, S.wold[t]);
+                S.ox[t] = ox;
+                S.oy[t] = oy;
+                S.oamp[t] = S.th_old[4 * t];
+                S.oinv2[t] = 1.0 / (2.0 * os * os);
+            }
+        }
+        for (int off = 1; off < m; off <<= 1) {
+            const int64_t v = __shfl_up((long long)area, off, 64);
+            if (t >= off) area += v;
+        }
+        if (t < m) S.pref[t + 1] = area;
+        if (t == 0) S.pref[0] = 0;
+    }
+    __syncthreads();
 }
 
 __device__ inline double wave_sum(double v)
@@ -710,7 +886,7 @@ __device__ void evaluate_tiles_mfma(const Params &p, WGShared &S, float *tile, i
     // 16 bi + 4 (l / 16) + r and column 16 bj + l % 16 of G.  Entry (i, k),
     // i <= k, of the output is G[k][i], taken from block (k / 16, i / 16).
     double *buf = reinterpret_cast<double *>(tile);
-    static_assert(2 * sizeof(double) * (kMaxN + 1) * (kMaxN + 2) / 2 <= kTileBytes, "wave sums");
+    static_assert(2 * sizeof(double) * (kMaxN + 1) * (kMaxN + 2) / 2 <= kRowOffset, "wave sums");
     for (int half = 0; half < 2; ++half) {
         if ((wave >> 1) == half) {
             double *dst = buf + (wave & 1) * n_out;
@@ -825,7 +1001,7 @@ __device__ __forceinline__ void evaluate_tiles_reg(const Params &p, WGShared &S,
     // half of them at a time, and lane q then adds value q over the 64 lanes
     // in lane order.  Rows are padded to 65 doubles against bank conflicts.
     constexpr int NV = NO + 3, HALF = (NV + 1) / 2, ROW = 65;
-    static_assert(sizeof(double) * (kT / 64) * HALF * ROW <= kTileBytes, "reduction buffer");
+    static_assert(sizeof(double) * (kT / 64) * HALF * ROW <= kRowOffset, "reduction buffer");
     double v[NV];
 #pragma unroll
     for (int o = 0; o < NO; ++o) v[o] = acc[o];
@@ -862,47 +1038,52 @@ __device__ __forceinline__ void evaluate_tiles_reg(const Params &p, WGShared &S,
     __syncthreads();
 }
 
-// Rows w0..w1-1 of the partials summed in row order.
+// Rows w0..w1-1 of the partials summed in row order, sixteen loads in flight.
 __device__ __forceinline__ double sum_column(const Params &p, int w0, int w1, int o)
 {
     double v = 0.0;
-    int w = w0;
-    for (; w + 4 <= w1; w += 4) {
-        const double a = ld_shared(p.partials + (int64_t)w * kPartStride + o);
-        const double b = ld_shared(p.partials + (int64_t)(w + 1) * kPartStride + o);
-        const double c = ld_shared(p.partials + (int64_t)(w + 2) * kPartStride + o);
-        const double d = ld_shared(p.partials + (int64_t)(w + 3) * kPartStride + o);
-        v += a; v += b; v += c; v += d;
+    for (int w = w0; w < w1; w += 16) {
+        double a[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u)
+            a[u] = w + u < w1 ? ld_shared(p.partials + (int64_t)(w + u) * kPartStride + o) : 0.0;
+#pragma unroll
+        for (int u = 0; u < 16; ++u)
+            if (w + u < w1) v += a[u];
     }
-    for (; w < w1; ++w) v += ld_shared(p.partials + (int64_t)w * kPartStride + o);
     return v;
 }
 
-__device__ __forceinline__ void sum_rows(const Params &p, int n, int w0, int w1, int dst)
+// Entry o of a trial's sums, to where the LM step reads it: He, S.ge, S.Fe,
+// S.chi2e, S.npx_e.
+__device__ __forceinline__ void put_sum(WGShared &S, double *He, int n, int o, double v)
 {
     const int n_out = (n + 1) * (n + 2) / 2;
-    for (int o = threadIdx.x; o < n_out + 3; o += kT)
-        p.partials[(int64_t)dst * kPartStride + o] = sum_column(p, w0, w1, o);
+    if (o >= n_out) {
+        if (o == n_out) S.Fe = v;
+        else if (o == n_out + 1) S.chi2e = v;
+        else S.npx_e = (int64_t)v;
+        return;
+    }
+    int i, k;
+    out_pair(o, n, i, k);
+    if (i < n && k < n) { He[i * n + k] = v; He[k * n + i] = v; }
+    else if (i < n) S.ge[i] = v;
 }
 
-// Rows w0..w1-1 summed in row order into He, S.ge, S.Fe, S.chi2e, S.npx_e.
+// Rows w0..w1-1 of the partials summed in row order into He, S.ge, S.Fe, ...
 __device__ __forceinline__ void reduce_partials(const Params &p, WGShared &S, int w0, int w1, double *He)
 {
-    const int n = S.n;
-    const int n_out = (n + 1) * (n + 2) / 2;
-    for (int o = threadIdx.x; o < n_out + 3; o += kT) {
-        const double v = sum_column(p, w0, w1, o);
-        if (o >= n_out) {
-            if (o == n_out) S.Fe = v;
-            else if (o == n_out + 1) S.chi2e = v;
-            else S.npx_e = (int64_t)v;
-            continue;
-        }
-        int i, k;
-        out_pair(o, n, i, k);
-        if (i < n && k < n) { He[i * n + k] = v; He[k * n + i] = v; }
-        else if (i < n) S.ge[i] = v;
-    }
+    const int n = S.n, nv = (n + 1) * (n + 2) / 2 + 3;
+    for (int o = threadIdx.x; o < nv; o += kT) put_sum(S, He, n, o, sum_column(p, w0, w1, o));
+    __syncthreads();
+}
+
+// The same of a trial the leader evaluated alone (its row in LDS).
+__device__ __forceinline__ void reduce_own(WGShared &S, const double *row, double *He)
+{
+    const int n = S.n, nv = (n + 1) * (n + 2) / 2 + 3;
+    for (int o = threadIdx.x; o < nv; o += kT) put_sum(S, He, n, o, 0.0 + row[o]);
     __syncthreads();
 }
 
@@ -1328,10 +1509,12 @@ __device__ __forceinline__ void commit(const Params &p, WGShared &S)
 
 // ---------------------------------------------------------------------------
 
-// Evaluate this work-group's tiles of the trial prepared in S into row.
-__device__ __forceinline__ void evaluate_row(const Params &p, WGShared &S, float *tile, double *red, int64_t tile0,
-                             int64_t stride, double *row)
+// Evaluate this work-group's tiles of the trial prepared in S; its partial row
+// is left in LDS (the returned pointer), complete for every thread.
+__device__ __forceinline__ double *evaluate_row(const Params &p, WGShared &S, float *tile, double *red,
+                                                int64_t tile0, int64_t stride)
 {
+    double *row = reinterpret_cast<double *>(reinterpret_cast<unsigned char *>(tile) + kRowOffset);
     if (S.m == 1) evaluate_tiles_reg<1>(p, S, tile0, stride, row, tile);
     else if (S.m == 2) evaluate_tiles_reg<2>(p, S, tile0, stride, row, tile);
     else if (S.m <= 3) evaluate_tiles_mfma<1>(p, S, tile, tile0, stride, row);
@@ -1339,6 +1522,7 @@ __device__ __forceinline__ void evaluate_row(const Params &p, WGShared &S, float
     else if (S.m <= 11) evaluate_tiles_mfma<3>(p, S, tile, tile0, stride, row);
     else if (S.m <= 15) evaluate_tiles_mfma<4>(p, S, tile, tile0, stride, row);
     else evaluate_tiles(p, S, tile, red, tile0, stride, row);
+    return row;
 }
 
 // Work-groups of a shared trial: at least min_tiles tiles each.
@@ -1348,111 +1532,103 @@ __device__ inline int eval_groups(int64_t ntiles, int nwg, int min_tiles)
     return (int)(want < nwg ? want : nwg);
 }
 
-// Arrival of one work-group after a shared trial (every work-group, every
-// round): the last of a group sums the group's evaluated rows in order into
-// the group row and arrives at the top counter.
-__device__ __forceinline__ void arrive(const Params &p, FitGlobal *G, WGShared &S, int wg, int nwg,
-                                       int geff, bool acquire = true)
+// Up to this many parameters the leader sums all the rows of a shared trial
+// itself (reduce_flat): a row is at most 48 values, and the second level's
+// hop between work-groups costs more than the reads.  Above, the last arrival
+// of a group sums the group's rows.
+constexpr int kFlatMaxN = 8;
+constexpr int kFlatMaxV = (kFlatMaxN + 1) * (kFlatMaxN + 2) / 2 + 3;
+static_assert(sizeof(double) * kFlatMaxV * kMaxGroups <= kRowOffset,
+              "group sums of the flat reduction in the tile buffer, before the leader's row");
+
+// One work-group's arrival after its tiles of a shared trial: the row goes to
+// the partials, then the group's counter moves.  With the flat sums that is
+// all (the leader keeps its own row in LDS and does not arrive); otherwise the
+// last evaluating work-group of the group sums the group's rows in order into
+// the group row, clears the counter and arrives at the top counter.
+__device__ __forceinline__ void arrive(const Params &p, FitGlobal *G, WGShared &S, const double *row,
+                                       int wg, int nwg, int geff)
 {
-    const int t = threadIdx.x;
-    const int gs = p.group;
-    const int grp = wg / gs;
-    const int gsize = (grp + 1) * gs < nwg ? gs : nwg - grp * gs;
-    const int ng_eval = (geff + gs - 1) / gs;
+    const int t = threadIdx.x, n = S.n;
+    const int nv = (n + 1) * (n + 2) / 2 + 3;
+    const int gs = p.group, grp = wg / gs;
+    double *dst = p.partials + (int64_t)wg * kPartStride;
+    if (n <= kFlatMaxN) {
+        static_assert(kFlatMaxV <= 64, "one wave stores the row");
+        if (t < 64) {
+            if (t < nv) st_shared(dst + t, row[t]);
+            wave_stores_done();
+            if (t == 0)
+                __hip_atomic_fetch_add(&G->arrive_g[grp].n, 1u, __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_AGENT);
+        }
+        return;
+    }
+    for (int o = t; o < nv; o += kT) st_shared(dst + o, row[o]);
+    wave_stores_done();
     __syncthreads();
+    const int r0 = grp * gs, r1 = r0 + gs < geff ? r0 + gs : geff;
     if (t == 0) {
-        // the group rows are read with atomic loads, so the acquire is optional
-        const unsigned prev =
-            acquire ? __hip_atomic_fetch_add(&G->arrive_g[grp], 1u, __ATOMIC_ACQ_REL,
-                                             __HIP_MEMORY_SCOPE_AGENT)
-                    : __hip_atomic_fetch_add(&G->arrive_g[grp], 1u, __ATOMIC_RELEASE,
-                                             __HIP_MEMORY_SCOPE_AGENT);
-        S.last = (prev == (unsigned)gsize - 1u) ? 1 : 0;
-        if (S.last)
-            __hip_atomic_store(&G->arrive_g[grp], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const unsigned prev = __hip_atomic_fetch_add(&G->arrive_g[grp].n, 1u, __ATOMIC_RELAXED,
+                                                     __HIP_MEMORY_SCOPE_AGENT);
+        S.last = (prev == (unsigned)(r1 - r0) - 1u) ? 1 : 0;
+        if (S.last) st_shared(&G->arrive_g[grp].n, 0u);
     }
     __syncthreads();
     if (!S.last) return;
-    const int r0 = grp * gs, r1 = (r0 + gs < geff) ? r0 + gs : geff;
-    if (ng_eval > 1 && r0 < r1) sum_rows(p, S.n, r0, r1, nwg + grp);
+    if (geff > gs) {
+        double *sum = p.partials + (int64_t)(nwg + grp) * kPartStride;
+        for (int o = t; o < nv; o += kT) st_shared(sum + o, sum_column(p, r0, r1, o));
+    }
+    wave_stores_done();
     __syncthreads();
-    if (t == 0) __hip_atomic_fetch_add(&G->top, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+    if (t == 0) __hip_atomic_fetch_add(&G->top.n, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Flat arrival of a shared trial of at most eight parameters (k_fit only):
-// every work-group, work-group 0 included, adds itself to its group's counter
-// with one release and leaves; no group sums its rows.  Work-group 0 waits for
-// every group (flat_wait), resets the counters, and sums all the evaluated rows
-// itself (reduce_flat), in the association of the two-level sums: rows in
-// order within a group of p.group, then the groups in order.
-constexpr int kFlatMaxN = 8;
-static_assert(sizeof(double) * ((kFlatMaxN + 1) * (kFlatMaxN + 2) / 2 + 3) * kMaxGroups <=
-                  kTileBytes, "group sums of the flat reduction in the tile buffer");
-__device__ __forceinline__ void arrive_flat(FitGlobal *G, int wg, int gs)
+// Arrival after a command that changed or read plain data (the residual).
+__device__ __forceinline__ void arrive_released(FitGlobal *G, int wg, int gs)
 {
+    wave_stores_done();
     __syncthreads();
     if (threadIdx.x == 0)
-        __hip_atomic_fetch_add(&G->arrive_g[wg / gs], 1u, __ATOMIC_RELEASE,
+        __hip_atomic_fetch_add(&G->arrive_g[wg / gs].n, 1u, __ATOMIC_RELEASE,
                                __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Work-group 0: lane g of wave 0 polls group g's counter until the group is
-// complete (every group of the grid, evaluating or not, so that no late
-// arrival can count toward the next trial), then clears it.  Bounded in time.
-__device__ __forceinline__ bool flat_wait(FitGlobal *G, WGShared &S, int nwg, int gs,
-                                          unsigned long long limit)
-{
-    const int t = threadIdx.x;
-    const int ngroups = (nwg + gs - 1) / gs;
-    if (t < 64) {
-        const int g = t;
-        const bool live = g < ngroups;
-        const unsigned need = live ? (unsigned)((g + 1) * gs < nwg ? gs : nwg - g * gs) : 0u;
-        const unsigned long long t0 = now_ticks();
-        bool ok = true;
-        for (;;) {
-            const unsigned v = live ? __hip_atomic_load(&G->arrive_g[g], __ATOMIC_RELAXED,
-                                                        __HIP_MEMORY_SCOPE_AGENT)
-                                    : 0u;
-            if (__all(v >= need)) break;
-            if (now_ticks() - t0 > limit) { ok = false; break; }
-            __builtin_amdgcn_s_sleep(kPollSleep);
-        }
-        if (live) __hip_atomic_store(&G->arrive_g[g], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (t == 0) S.abort = ok ? 0 : 1;
-    }
-    __syncthreads();
-    return S.abort == 0;
-}
-
-// The evaluated rows 0 .. geff-1 summed into He, S.ge, S.Fe, S.chi2e, S.npx_e
-// with the two-level association; `scratch` holds the group sums
-// ((n_out + 3) x groups doubles, LDS).
+// The evaluated rows 0 .. geff-1 (row 0 the leader's own, in LDS) summed into
+// He, S.ge, S.Fe, S.chi2e, S.npx_e in the association of the two-level sums:
+// rows in order within a group, then the groups in order.  `scratch` holds the
+// group sums ((n_out + 3) x groups doubles, LDS).
 __device__ __forceinline__ void reduce_flat(const Params &p, WGShared &S, int geff, int gs,
-                                            double *He, double *scratch)
+                                            const double *row, double *He, double *scratch)
 {
     const int n = S.n;
-    const int n_out = (n + 1) * (n + 2) / 2, nv = n_out + 3;
+    const int nv = (n + 1) * (n + 2) / 2 + 3;
     const int ng = (geff + gs - 1) / gs;
     for (int e = threadIdx.x; e < nv * ng; e += kT) {
         const int o = e % nv, g = e / nv;
         const int r0 = g * gs, r1 = r0 + gs < geff ? r0 + gs : geff;
-        scratch[g * nv + o] = sum_column(p, r0, r1, o);
+        double v = 0.0;
+        for (int w = r0; w < r1; w += 16) {
+            double a[16];
+#pragma unroll
+            for (int u = 0; u < 16; ++u) {
+                a[u] = 0.0;
+                if (w + u > 0 && w + u < r1)
+                    a[u] = ld_shared(p.partials + (int64_t)(w + u) * kPartStride + o);
+            }
+            if (w == 0) a[0] = row[o];
+#pragma unroll
+            for (int u = 0; u < 16; ++u)
+                if (w + u < r1) v += a[u];
+        }
+        scratch[g * nv + o] = v;
     }
     __syncthreads();
     for (int o = threadIdx.x; o < nv; o += kT) {
         double v = scratch[o];
         for (int g = 1; g < ng; ++g) v += scratch[g * nv + o];
-        if (o >= n_out) {
-            if (o == n_out) S.Fe = v;
-            else if (o == n_out + 1) S.chi2e = v;
-            else S.npx_e = (int64_t)v;
-            continue;
-        }
-        int i, k;
-        out_pair(o, n, i, k);
-        if (i < n && k < n) { He[i * n + k] = v; He[k * n + i] = v; }
-        else if (i < n) S.ge[i] = v;
+        put_sum(S, He, n, o, v);
     }
     __syncthreads();
 }
@@ -1463,7 +1639,7 @@ __device__ __forceinline__ void reduce_flat(const Params &p, WGShared &S, int ge
 __device__ __forceinline__ void fit_begin(const Params &p, WGShared &S, bool abort)
 {
     DevState *st = p.st;
-    atomicAdd(&st->prof[kPFits], 1ull);
+    S.prof[kPFits] += 1ull;
     st->fit_ready = 0;
     const unsigned long long key = S.key;
     int64_t idx = st->forced_idx >= 0
@@ -1496,96 +1672,89 @@ __device__ __forceinline__ void fit_begin(const Params &p, WGShared &S, bool abo
 // One evaluation of the trial at S.th_e (old members at S.th_old) by the
 // leading work-group: F, chi2, the pixel count and [J r]^T [J r] reduced into
 // S.Fe, S.chi2e, S.npx_e, S.ge and the Gram buffer H2 + (1 - S.hsel) n^2.  A
-// trial larger than p.solo_tiles tiles is published (with G->cmd = cmd when
-// cmd != 0) and shared by the nwg work-groups.  Returns false when a wait ran
-// out; the context is then marked with ASP_ERR_DEVICE.
+// trial larger than p.solo_tiles tiles is published (with the field, for a
+// batch team) and shared by the nwg work-groups.  Returns false when a wait
+// ran out; the context is then marked with ASP_ERR_DEVICE.
 __device__ __forceinline__ bool trial_eval(const Params &p, FitGlobal *G, WGShared &S, float *tile,
-                                           double *red, double *H2, int nwg, int cmd)
+                                           double *red, double *H2, int nwg, int field)
 {
     DevState *st = p.st;
     const int t = threadIdx.x;
-    const int ngroups = (nwg + p.group - 1) / p.group;
-    prepare(p, S, S.m, S.th_e, S.th_old);
+    prepare(p, S);
     const int64_t ntiles = (S.pref[S.m] + kT - 1) / kT;
-    lap(p, S, kPPrepare);
+    lap(S, kPPrepare);
     double *He = H2 + (1 - S.hsel) * (kMaxN * kMaxN);   // the trial's buffer
     if (ntiles <= p.solo_tiles) {
         // small: the leading work-group alone, no publication
-        if (t == 0) atomicAdd(&p.st->prof[kPSoloTrials], 1ull);
-        evaluate_row(p, S, tile, red, 0, 1, p.partials);
-        lap(p, S, kPEval);
-        reduce_partials(p, S, 0, 1, He);
-        lap(p, S, kPReduce);
-        if (t == 0) atomicAdd(&p.st->prof[kPSoloPx], (unsigned long long)S.npx_e);
+        const double *row = evaluate_row(p, S, tile, red, 0, 1);
+        lap(S, kPEval);
+        reduce_own(S, row, He);
+        lap(S, kPReduce);
+        if (t == 0) {
+            S.prof[kPSoloTrials] += 1ull;
+            S.prof[kPSoloPx] += (unsigned long long)S.npx_e;
+        }
         return true;
     }
     // large: every work-group takes a share
     const int geff = eval_groups(ntiles, nwg, p.min_tiles);
     const int ng_eval = (geff + p.group - 1) / p.group;
-    if (t < S.n) G->th_e[t] = S.th_e[t];
-    if (t == 0 && cmd) G->cmd = cmd;
-    publish(G);
-    evaluate_row(p, S, tile, red, 0, geff, p.partials);
-    lap(p, S, kPEval);
-    if (cmd == 0 && S.n <= kFlatMaxN) {
-        arrive_flat(G, 0, p.group);
-        lap(p, S, kPArrive);
-        const bool ok = flat_wait(G, S, nwg, p.group, p.spin_ticks);
-        lap(p, S, kPWait);
-        if (!ok) {
-            if (t == 0) st->stop = ASP_ERR_DEVICE;
-            __syncthreads();
-            return false;
+    // a batch's leader may have changed R since its last message
+    publish(G, S, kCmdEval, geff, field, S.epoch != S.epoch_have);
+    if (t == 0) S.epoch_have = S.epoch;
+    const double *row = evaluate_row(p, S, tile, red, 0, geff);
+    lap(S, kPEval);
+    bool ok;
+    if (S.n <= kFlatMaxN) {
+        ok = wait_groups(G, S, geff, p.group, p.spin_ticks);
+        lap(S, kPWait);
+    } else {
+        arrive(p, G, S, row, 0, nwg, geff);
+        lap(S, kPArrive);
+        if (t == 0) {
+            S.abort = spin_until(&G->top.n, (unsigned)ng_eval, p.spin_ticks) ? 0 : 1;
+            st_shared(&G->top.n, 0u);
         }
-        reduce_flat(p, S, geff, p.group, He, reinterpret_cast<double *>(tile));
-        lap(p, S, kPReduce);
-        return true;
+        __syncthreads();
+        lap(S, kPWait);
+        ok = S.abort == 0;
     }
-    arrive(p, G, S, 0, nwg, geff, false);
-    lap(p, S, kPArrive);
-    if (t == 0) {
-        // the rows are read with atomic loads: no acquire
-        S.abort = spin_until(&G->top, (unsigned)ngroups, p.spin_ticks, false) ? 0 : 1;
-        __hip_atomic_store(&G->top, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    lap(p, S, kPWait);
-    __syncthreads();
-    if (S.abort) {
+    if (!ok) {
         if (t == 0) st->stop = ASP_ERR_DEVICE;
         __syncthreads();
         return false;
     }
-    if (ng_eval > 1) reduce_partials(p, S, nwg, nwg + ng_eval, He);
+    if (S.n <= kFlatMaxN)
+        reduce_flat(p, S, geff, p.group, row, He, reinterpret_cast<double *>(tile));
+    else if (ng_eval > 1) reduce_partials(p, S, nwg, nwg + ng_eval, He);
     else reduce_partials(p, S, 0, geff, He);
-    lap(p, S, kPReduce);
+    lap(S, kPReduce);
     return true;
 }
 
 // Start values, active set, the LM trials and the commit of one fit, by the
-// leading work-group (share 0 of nwg).  A trial larger than p.solo_tiles tiles
-// is published (with G->cmd = cmd when cmd != 0) and shared by the nwg
-// work-groups.  Returns false when a wait ran out; the context is then marked
-// with ASP_ERR_DEVICE.
+// leading work-group (share 0 of nwg).  Returns false when a wait ran out; the
+// context is then marked with ASP_ERR_DEVICE.
 __device__ __forceinline__ bool fit_trials(const Params &p, FitGlobal *G, WGShared &S, float *tile,
                                            double *red, double *A, double *H2,
-                                           int nwg, int cmd)
+                                           int nwg, int field)
 {
     DevState *st = p.st;
     const int t = threadIdx.x;
     mark(S);
     if (t == 0) S.tfit = S.tmark;
-    setup_fit(p, G, S, S.use_prop != 0);
-    lap(p, S, kPSetup);
+    setup_fit(p, S, S.use_prop != 0);
+    lap(S, kPSetup);
     for (;;) {
-        if (!trial_eval(p, G, S, tile, red, H2, nwg, cmd)) return false;
+        if (!trial_eval(p, G, S, tile, red, H2, nwg, field)) return false;
         lm_step(p, S, H2, A);
-        lap(p, S, kPLmStep);
+        lap(S, kPLmStep);
         if (t == 0) {
             const unsigned long long npx = (unsigned long long)S.npx_e;
-            st->sum_eval_px += npx;
-            st->sum_gram_flops += npx * (unsigned long long)((S.n + 1) * (S.n + 2));
-            atomicAdd(&st->prof[kPTrials], 1ull);
-            atomicAdd(&st->prof[kPEvalPx], npx);
+            S.eval_px += npx;
+            S.gram_flops += npx * (unsigned long long)((S.n + 1) * (S.n + 2));
+            S.prof[kPTrials] += 1ull;
+            S.prof[kPEvalPx] += npx;
         }
         if (!S.finished) continue;
         if (S.use_prop && S.chose_prop && S.pass == 0 && (!S.converged || S.th_c[0] == 0.0)) {
@@ -1599,18 +1768,19 @@ __device__ __forceinline__ bool fit_trials(const Params &p, FitGlobal *G, WGShar
                 S.pass = 1;
             }
             __syncthreads();
-            setup_fit(p, G, S, false);
+            setup_fit(p, S, false);
             continue;
         }
         mark(S);
         commit(p, S);
-        lap(p, S, kPCommit);
+        lap(S, kPCommit);
         if (t == 0) {
             const int m = S.m;
             st->fits_m[m] += 1ull;
             st->trials_m[m] += (unsigned long long)(S.trials_total + S.trials);
             st->ticks_m[m] += now_ticks() - S.tfit;
         }
+        flush_counts(p, S);
         return true;
     }
 }
@@ -1632,56 +1802,54 @@ __global__ __launch_bounds__(kT) void k_fit(Params p)
     // work-group has checked in, so all of them agree here.
     if (st->stop && st->diag_m == 0) return;
 
-    mark(S);
-    // Check in: every work-group reads the generation before work-group 0 may
-    // publish.
+    // Check in: every work-group reads the last message's number before
+    // work-group 0 may publish.
     if (t == 0) {
-        S.gen = __hip_atomic_load(&G->gen, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        S.abort = 0;
-        __hip_atomic_fetch_add(&G->top, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        mail_begin(G, S);
+        if (wg != 0) {
+            // the number has been read
+            wave_stores_done();
+            __hip_atomic_fetch_add(&G->top.n, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
     }
     __syncthreads();
+    mark(S);
 
     if (wg != 0) {
         // Workers: evaluate the shared trials work-group 0 publishes.
-        // The residual does not change inside this kernel and everything
-        // published is read with atomic loads, so the workers need no acquire
-        // fence: their L2 keeps the residual's lines from trial to trial.
+        // The residual does not change before the update at the end of this
+        // kernel and everything else that crosses is read with atomic loads, so
+        // the workers need no acquire fence: their L2 keeps the residual's
+        // lines from trial to trial.
         for (;;) {
-            if (!wait_publish(G, S, p.spin_ticks, false)) {
+            if (!wait_mail(G, S, wg, p.spin_ticks)) {
                 if (t == 0) st->stop = ASP_ERR_DEVICE;
                 return;
             }
-            if (t == 0) {
-                S.done = ld_shared(&G->done);
-                S.cmd = ld_shared(&G->m);
-            }
-            __syncthreads();
-            if (S.done) {
-                if (S.done == 2) {
-                    // the committed plan was written by work-group 0 with plain
-                    // stores: acquire before reading it
-                    if (t == 0) acquire_fence();
-                    __syncthreads();
-                    update_tiles(p, wg, nwg, tile);
-                }
+            if (S.cmd == kCmdUpdate) {
+                // the committed plan was written by work-group 0 with plain
+                // stores: acquire before reading it
+                if (t == 0) acquire_fence();
+                __syncthreads();
+                update_tiles(p, wg, nwg, tile);
                 return;
             }
-            prepare(p, S, S.cmd, G->th_e, G->th_old, true);
-            const int64_t ntiles = (S.pref[S.m] + kT - 1) / kT;
-            const int geff = eval_groups(ntiles, nwg, p.min_tiles);
-            if (wg < geff)
-                evaluate_row(p, S, tile, red, wg, geff, p.partials + (int64_t)wg * kPartStride);
-            if (S.n <= kFlatMaxN) arrive_flat(G, wg, p.group);
-            else arrive(p, G, S, wg, nwg, geff, false);
+            if (S.cmd != kCmdEval) return;
+            const int geff = S.geff;
+            if (wg < geff) {
+                prepare(p, S);
+                const double *row = evaluate_row(p, S, tile, red, wg, geff);
+                arrive(p, G, S, row, wg, nwg, geff);
+            }
+            __syncthreads();               // S is rewritten by the next message
         }
     }
 
     // Work-group 0 drives the fit.
     if (t == 0) {
-        S.abort = spin_until(&G->top, (unsigned)nwg, p.spin_ticks) ? 0 : 1;
-        __hip_atomic_store(&G->top, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        lap(p, S, kPCheckin);
+        S.abort = spin_until(&G->top.n, (unsigned)nwg - 1u, p.spin_ticks) ? 0 : 1;
+        st_shared(&G->top.n, 0u);
+        lap(S, kPCheckin);
     }
     __syncthreads();
     if (st->diag_m > 0) {
@@ -1691,15 +1859,11 @@ __global__ __launch_bounds__(kT) void k_fit(Params p)
             S.m = st->diag_m;
             S.n = 4 * S.m;
             S.hsel = 0;
-            G->m = S.m;
-            G->n = S.n;
-            G->done = 0;
         }
         __syncthreads();
         if (t < S.n) {
             S.th_e[t] = st->diag_theta[t];
             S.th_old[t] = st->diag_stored[t];
-            G->th_old[t] = S.th_old[t];
         }
         __syncthreads();
         const bool ok = !S.abort && trial_eval(p, G, S, tile, red, H2, nwg, 0);
@@ -1718,16 +1882,15 @@ __global__ __launch_bounds__(kT) void k_fit(Params p)
         if (t == 0) {
             if (!ok) st->stop = ASP_ERR_DEVICE;
             st->diag_m = 0;
-            G->done = 1;
         }
-        publish(G);
+        flush_counts(p, S);
+        publish(G, S, kCmdExit);
         return;
     }
     collect_peak_key(st, true, &S.key);
     if (t == 0) {
         fit_begin(p, S, S.abort != 0);
-        // workers read this only after a publication of this fit
-        G->done = S.stop ? 1 : 0;
+        S.upd = 0;
     }
     __syncthreads();
     if (!S.stop) {
@@ -1735,13 +1898,14 @@ __global__ __launch_bounds__(kT) void k_fit(Params p)
         // with fuse_update every work-group takes its tiles of the update
         // (Sect. 2 step 3) after this publication; the end of the kernel is
         // the barrier before the next iteration reads R
-        if (t == 0) {
-            S.upd = committed && p.fuse_update ? 1 : 0;
-            G->done = S.upd ? 2 : 1;
-        }
+        if (t == 0) S.upd = committed && p.fuse_update ? 1 : 0;
+    } else {
+        flush_counts(p, S);
     }
-    publish(G);
-    if (!S.stop && S.upd) update_tiles(p, 0, nwg, tile);
+    __syncthreads();
+    const bool upd = S.upd != 0;
+    publish(G, S, upd ? kCmdUpdate : kCmdExit, 0, 0, upd);
+    if (upd) update_tiles(p, 0, nwg, tile);
 }
 
 // ===========================================================================
@@ -1756,8 +1920,6 @@ __global__ __launch_bounds__(kT) void k_fit(Params p)
 // the residual update, or exit.  Every command is acknowledged by every member
 // before the next one is published; every wait is bounded.
 // ===========================================================================
-
-enum { kCmdPeak = 1, kCmdEval = 2, kCmdUpdate = 3, kCmdExit = 4 };
 
 // The field's parameters with the team's exchange buffers and the batch's
 // tile thresholds (thread 0 writes, the work-group reads after the barrier).
@@ -1776,16 +1938,14 @@ __device__ __forceinline__ void load_field(const BatchArgs &b, int f, FitGlobal 
     __syncthreads();
 }
 
-// The leader's wait for the team's arrivals; false when it ran out.
-__device__ __forceinline__ bool team_wait(FitGlobal *G, WGShared &S, int ngroups,
-                                          unsigned long long limit)
+// The leader's wait for the team's arrivals after a command on plain data, and
+// the acquire of what they wrote; false when it ran out.
+__device__ __forceinline__ bool team_wait(FitGlobal *G, WGShared &S, int T, unsigned long long limit)
 {
-    if (threadIdx.x == 0) {
-        S.abort = spin_until(&G->top, (unsigned)ngroups, limit) ? 0 : 1;
-        __hip_atomic_store(&G->top, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
+    const bool ok = wait_groups(G, S, T, kGroup, limit);
+    if (threadIdx.x == 0) acquire_fence();
     __syncthreads();
-    return S.abort == 0;
+    return ok;
 }
 
 __global__ __launch_bounds__(kT) void k_batch(BatchArgs b)
@@ -1804,56 +1964,63 @@ __global__ __launch_bounds__(kT) void k_batch(BatchArgs b)
     const int xcd = (int)blockIdx.x % 8, slot = (int)blockIdx.x / 8;
     const int team = xcd * (per_xcd / T) + slot / T;
     const int rank = slot % T;
-    const int ngroups = (T + kGroup - 1) / kGroup;
     FitGlobal *G = b.fg + team;
-    double *parts = b.partials + (int64_t)team * (T + ngroups) * kPartStride;
+    double *parts = b.partials + (int64_t)team * (T + (T + kGroup - 1) / kGroup) * kPartStride;
 
-    // check in: every follower reads the generation before the leader publishes
+    // check in: every follower reads the last message's number before the
+    // leader publishes
     if (t == 0) {
-        S.gen = __hip_atomic_load(&G->gen, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        S.abort = 0;
+        mail_begin(G, S);
         cur_field = -1;
-        if (rank != 0)
-            __hip_atomic_fetch_add(&G->top, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (rank != 0) {
+            wave_stores_done();
+            __hip_atomic_fetch_add(&G->top.n, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
     }
     __syncthreads();
 
     if (rank != 0) {
         for (;;) {
-            if (!wait_publish(G, S, b.spin_ticks, true, true)) return;  // the leader marks its field
-            if (t == 0) {
-                S.cmd = G->cmd;
-                S.fld = G->field;
-            }
-            __syncthreads();
+            if (!wait_mail(G, S, rank, b.spin_ticks, true)) return;  // the leader marks its field
             const int cmd = S.cmd;
             if (cmd == kCmdExit || S.fld < 0 || S.fld >= b.n_fields) return;
+            if (S.epoch != S.epoch_have) {
+                // R or the update's plan changed since this work-group's last
+                // acquire (messages may have been skipped: the epoch tells)
+                __syncthreads();
+                if (t == 0) {
+                    acquire_fence();
+                    S.epoch_have = S.epoch;
+                }
+                __syncthreads();
+            }
             if (S.fld != cur_field) {
                 load_field(b, S.fld, G, parts, P);
                 if (t == 0) cur_field = S.fld;
                 __syncthreads();
             }
-            int geff = 0;
             if (cmd == kCmdPeak) {
                 peak_scan(P.R, P.H * P.W, (uint32_t)rank, (uint32_t)T, P.st->peak_keys);
+                arrive_released(G, rank, kGroup);
             } else if (cmd == kCmdUpdate) {
                 update_tiles<1>(P, rank, T, tile);
+                arrive_released(G, rank, kGroup);
             } else if (cmd == kCmdEval) {
-                prepare(P, S, ld_shared(&G->m), G->th_e, G->th_old, true);
-                const int64_t ntiles = (S.pref[S.m] + kT - 1) / kT;
-                geff = eval_groups(ntiles, T, P.min_tiles);
-                if (rank < geff)
-                    evaluate_row(P, S, tile, red, rank, geff,
-                                 P.partials + (int64_t)rank * kPartStride);
+                const int geff = S.geff;
+                if (rank < geff) {
+                    prepare(P, S);
+                    const double *row = evaluate_row(P, S, tile, red, rank, geff);
+                    arrive(P, G, S, row, rank, T, geff);
+                }
             }
-            arrive(P, G, S, rank, T, geff);
+            __syncthreads();               // S is rewritten by the next message
         }
     }
 
     // the leader
     if (t == 0) {
-        if (T > 1) S.abort = spin_until(&G->top, (unsigned)(T - 1), b.spin_ticks) ? 0 : 1;
-        __hip_atomic_store(&G->top, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (T > 1) S.abort = spin_until(&G->top.n, (unsigned)(T - 1), b.spin_ticks) ? 0 : 1;
+        st_shared(&G->top.n, 0u);
     }
     __syncthreads();
     bool ok = S.abort == 0;
@@ -1867,14 +2034,14 @@ __global__ __launch_bounds__(kT) void k_batch(BatchArgs b)
         load_field(b, S.fld, G, parts, P);
         if (t == 0) {
             cur_field = S.fld;
-            G->field = S.fld;
+            S.epoch += 1u;             // another residual
             S.k_target = P.st->k + b.n_iter;
         }
         for (;;) {
             if (t == 0) {
                 S.go = (P.st->stop == 0 && P.st->k < S.k_target) ? 1 : 0;
                 // one heartbeat per iteration: the followers' waits restart
-                __hip_atomic_fetch_add(&G->beat, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_fetch_add(&G->beat.n, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
             __syncthreads();
             if (!S.go) break;
@@ -1883,11 +2050,10 @@ __global__ __launch_bounds__(kT) void k_batch(BatchArgs b)
             if (T == 1 || npx <= b.solo_peak_px) {
                 peak_scan(P.R, npx, 0u, 1u, P.st->peak_keys);
             } else {
-                if (t == 0) G->cmd = kCmdPeak;
-                publish(G);
+                publish(G, S, kCmdPeak, 0, cur_field, true);
+                if (t == 0) S.epoch_have = S.epoch;
                 peak_scan(P.R, npx, 0u, (uint32_t)T, P.st->peak_keys);
-                arrive(P, G, S, 0, T, 0);
-                if (!team_wait(G, S, ngroups, b.spin_ticks)) { ok = false; break; }
+                if (!team_wait(G, S, T, b.spin_ticks)) { ok = false; break; }
             }
             __syncthreads();
             // the stop test and the fit (Sect. 2 step 4; Sect. 3)
@@ -1895,7 +2061,7 @@ __global__ __launch_bounds__(kT) void k_batch(BatchArgs b)
             if (t == 0) fit_begin(P, S, false);
             __syncthreads();
             if (S.stop) break;
-            if (!fit_trials(P, G, S, tile, red, A, H2, T, kCmdEval)) { ok = false; break; }
+            if (!fit_trials(P, G, S, tile, red, A, H2, T, cur_field)) { ok = false; break; }
             // the residual update (Sect. 2 step 3)
             if (t == 0) {
                 const int32_t *bb = P.st->bb;
@@ -1905,20 +2071,18 @@ __global__ __launch_bounds__(kT) void k_batch(BatchArgs b)
             if (T == 1 || S.upx <= b.solo_update_px) {
                 update_tiles<1>(P, 0, 1, tile);
             } else {
-                if (t == 0) G->cmd = kCmdUpdate;
-                publish(G);
+                if (t == 0) S.epoch += 1u;     // the plan
+                publish(G, S, kCmdUpdate, 0, cur_field, true);
                 update_tiles<1>(P, 0, T, tile);
-                arrive(P, G, S, 0, T, 0);
-                if (!team_wait(G, S, ngroups, b.spin_ticks)) { ok = false; break; }
+                if (!team_wait(G, S, T, b.spin_ticks)) { ok = false; break; }
             }
+            __syncthreads();
+            if (t == 0) S.epoch += 1u;         // R
         }
     }
     if (!ok && t == 0 && cur_field >= 0) P.st->stop = ASP_ERR_DEVICE;
     __syncthreads();
-    if (T > 1) {
-        if (t == 0) G->cmd = kCmdExit;
-        publish(G);
-    }
+    if (T > 1) publish(G, S, kCmdExit, 0, 0, true);
 }
 
 __global__ void k_batch_reset(unsigned int *queue) { *queue = 0u; }
