@@ -46,13 +46,12 @@ constexpr int kT = kFitThreads;
 constexpr int kOwnMax = (kNOutMax + kT - 1) / kT;
 constexpr size_t kTileBytes = sizeof(float) * kT * kTileStride;
 constexpr size_t kMatBytes = sizeof(double) * kMaxN * kMaxN;
-constexpr size_t kFitLds = kTileBytes + 2 * kMatBytes;   // tile (or A) | two Gram buffers
+constexpr size_t kFitLds = kTileBytes + 2 * kMatBytes;   // tile (or L) | two Gram buffers
 // The work-group's own partial row, at the end of the tile buffer: it is
 // written when the tile is no longer read.
 constexpr size_t kRowOffset = kTileBytes - sizeof(double) * kPartStride;
 static_assert(kRowOffset % sizeof(double) == 0, "row alignment");
 constexpr int kGroup = 16;        // work-groups per first-level arrival group
-static_assert(kTileBytes >= kMatBytes, "A shares the tile buffer");
 static_assert(kTileBytes >= sizeof(float) * kUpdTabFloats, "the update's tables share the tile buffer");
 
 // Phase timer slots of DevState::prof.
@@ -66,17 +65,28 @@ __device__ inline unsigned long long now_ticks() { return wall_clock64(); }
 // counter another work-group advances (fewer reads of one line while waiting).
 constexpr int kPollSleep = 8;
 
+// A member at the parameters under evaluation, and an old member's stored
+// Gaussian: one run of 16-byte LDS reads each.
+struct alignas(16) Member {
+    double x, y, amp, inv2, invs2, invs3;   // 1 / (2 s^2), 1 / s^2, 1 / s^3
+    int32_t win[4];
+    double inv_wc;                          // 1 / columns of the window
+    int64_t wc;
+};
+struct alignas(16) Stored {
+    double x, y, amp, inv2;
+    int32_t win[4];
+};
+
 struct WGShared {
-    // member constants at the parameters under evaluation
-    int32_t win[kMaxM][4], wold[kMaxM][4];
+    Member mem[kMaxM];
+    Stored old[kMaxM];
     int64_t pref[kMaxM + 1];
-    double mx[kMaxM], my[kMaxM], mamp[kMaxM], minv2[kMaxM], minvs2[kMaxM], minvs3[kMaxM];
-    double ox[kMaxM], oy[kMaxM], oamp[kMaxM], oinv2[kMaxM];
     int32_t m, n;
     double wsum[4][3];
     unsigned long long prof[kProfSlots];   // phase timers and counts of this fit (leader)
     unsigned long long eval_px, gram_flops;   // of this fit's trials (thread 0 of the leader)
-    double wred[kT / 64][48];
+    double wred[kT / 64][4][48];
     // the reduced trial (work-group 0)
     double ge[kMaxN], Fe, chi2e;
     int64_t npx_e;
@@ -86,7 +96,7 @@ struct WGShared {
     // work-groups receive them as 32-bit halves
     union { double th_e[kMaxN]; uint32_t th_e32[2 * kMaxN]; };
     union { double th_old[kMaxN]; uint32_t th_old32[2 * kMaxN]; };
-    double dd[kMaxN], rhs[kMaxN], rhs_copy[kMaxN], delta[kMaxN];
+    double dd[kMaxN], rhs[kMaxN], delta[kMaxN];
     double ldiag[kMaxN];           // L_kk of the work-group Cholesky
     int32_t frozen[kMaxN];
     double F_c, chi2_c, mu, nu, pred, chi2_init, peak;
@@ -111,11 +121,12 @@ struct WGShared {
     unsigned int fit_no;           // leader: the fit's number, 0 before its first trial
     unsigned int fit_have;         // others: the fit whose th_old is held
     unsigned int epoch, epoch_have;   // of R (batched fields)
-    int32_t geff, poll_n;
+    int32_t geff, poll_n;          // geff: work-groups of the trial, 0 = the leader alone
     // control
     unsigned long long tmark;      // phase timer mark (thread 0)
     unsigned long long tfit;       // start of the fit (thread 0)
-    int32_t last, abort, done, ok, finished, accept, stop;
+    int32_t fresh;                 // the message opened a fit: th_old is new
+    int32_t last, abort, solve, pd, ok, finished, accept, stop;
     int32_t upd;                   // the fit committed and this launch also updates R
 };
 
@@ -151,6 +162,20 @@ __device__ __forceinline__ void flush_counts(const Params &p, WGShared &S)
     S.eval_px = S.gram_flops = 0ull;
 }
 
+// Orders the LDS accesses of one wave: the lanes of a wave issue LDS
+// instructions together and the LDS serves them in program order, so after
+// this point every lane sees what any lane of the wave wrote before it; the
+// wavefront-scope fences keep the compiler from moving accesses across.
+__device__ __forceinline__ void wave_lds_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// A condition that is the same in every lane, as a scalar.
+__device__ __forceinline__ bool uniform(bool b) { return __builtin_amdgcn_readfirstlane(b ? 1 : 0) != 0; }
+
 // ---------------------------------------------------------------------------
 // Synchronisation between work-groups.  Polling is relaxed (no cache
 // maintenance per poll).  Data written with ordinary stores (the residual, the
@@ -177,18 +202,15 @@ __device__ inline void wave_stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::
 
 enum { kCmdPeak = 1, kCmdEval = 2, kCmdUpdate = 3, kCmdExit = 4 };
 
-// The leader's next message (the whole work-group calls it): a command, and
-// with kCmdEval the trial point S.th_e for geff work-groups, with the old
-// members' stored parameters before the first trial of a fit.  release: plain
-// stores of this work-group go before it.
-__device__ __forceinline__ void publish(FitGlobal *G, WGShared &S, int cmd, int geff = 0,
-                                        int field = 0, bool release = false)
+// The leader's next message, by its wave 0: a command, and with kCmdEval the
+// trial point S.th_e for geff work-groups, with the old members' stored
+// parameters before the first trial of a fit.  release: the work-group's plain
+// stores go before it (each wave has waited for its own, and a barrier).
+__device__ __forceinline__ void post(FitGlobal *G, WGShared &S, int cmd, int geff, int field,
+                                     bool release)
 {
     static_assert(kMaxM < 32 && kCmdExit < 8 && kMaxGroups * kGroup < (1 << 24), "header bits");
-    if (release) wave_stores_done();
-    __syncthreads();
     const int t = threadIdx.x;
-    if (t >= 64) return;
     // the counters reset after the last trial are in place before this message
     wave_stores_done();
     if (release) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
@@ -197,9 +219,6 @@ __device__ __forceinline__ void publish(FitGlobal *G, WGShared &S, int cmd, int 
     const unsigned int fit_no = first ? gen : S.fit_no;
     const unsigned long long tag = (unsigned long long)gen << 32;
     const int nw = cmd == kCmdEval ? 2 * S.n : 0;
-    if (first)
-        for (int w = 8 + t; w < nw; w += 64)
-            st_shared(&G->old[w], ((unsigned long long)fit_no << 32) | S.th_old32[w]);
     for (int w = t; w < kMailHead + nw; w += 64) {
         uint32_t v;
         if (w == 0) v = (nw ? (uint32_t)S.m : 0u) | ((uint32_t)cmd << 5) | ((uint32_t)geff << 8);
@@ -209,21 +228,35 @@ __device__ __forceinline__ void publish(FitGlobal *G, WGShared &S, int cmd, int 
         else v = S.th_e32[w - kMailHead];
         st_shared(&G->mail[w], tag | v);
     }
+    if (first)
+        for (int w = 8 + t; w < nw; w += 64)
+            st_shared(&G->old[w], ((unsigned long long)fit_no << 32) | S.th_old32[w]);
     if (t == 0) {
         S.gen = gen;
         if (first) S.fit_no = fit_no;
     }
+    wave_lds_sync();
+}
+
+// A message by the whole work-group.
+__device__ __forceinline__ void publish(FitGlobal *G, WGShared &S, int cmd, int field = 0,
+                                        bool release = false)
+{
+    if (release) wave_stores_done();
+    __syncthreads();
+    if (threadIdx.x < 64) post(G, S, cmd, 0, field, release);
 }
 
 // The next message, into S (command, geff, field, epoch and, for a trial in
-// which work-group `wg` has tiles, m, n, th_e and th_old).  Wave 0 polls the
-// words the last one had.  A work-group without tiles may find that the
+// which work-group `wg` has tiles, m, n, th_e and th_old); S.abort when none
+// came.  For wave 0; a barrier follows before the others read S.  It polls the
+// words the last message had.  A work-group without tiles may find that the
 // leader has moved on; one with tiles cannot, as the leader waits for it.
 // Bounded in time: `limit` device wall-clock ticks.  With `beat`, the bound
 // restarts whenever the heartbeat moves: a leader that works alone for a long
 // time (small fields of a batch) keeps its followers waiting without letting
 // them time out.
-__device__ __forceinline__ bool wait_mail(FitGlobal *G, WGShared &S, int wg,
+__device__ __forceinline__ void wait_mail(FitGlobal *G, WGShared &S, int wg,
                                           unsigned long long limit, bool beat = false)
 {
     const int t = threadIdx.x;
@@ -273,7 +306,8 @@ __device__ __forceinline__ bool wait_mail(FitGlobal *G, WGShared &S, int wg,
             }
             const unsigned int fit_no = (unsigned int)__builtin_amdgcn_readlane((int)(uint32_t)w, 1);
             const int no = 8 * (int)(head & 31u);
-            if (mine && fit_no != S.fit_have) {
+            const bool fresh = mine && fit_no != S.fit_have;
+            if (fresh) {
                 for (int b = 0; b < no && ok; b += 64) {
                     const int i = b + t;
                     const bool want = i >= 8 && i < no;
@@ -299,15 +333,15 @@ __device__ __forceinline__ bool wait_mail(FitGlobal *G, WGShared &S, int wg,
                     S.n = 4 * S.m;
                     S.poll_n = need < 64 ? need : 64;
                 }
+                S.fresh = fresh ? 1 : 0;
             }
         }
         if (t == 0) {
             S.gen = gen;
             S.abort = ok ? 0 : 1;
         }
+        wave_lds_sync();
     }
-    __syncthreads();
-    return S.abort == 0;
 }
 
 // Before the first message of a launch: the number of the last one, and
@@ -440,13 +474,14 @@ __device__ __forceinline__ void setup_fit(const Params &p, WGShared &S, bool use
         S.sel[0] = t0[1];
         S.sel[1] = t0[2];
         S.sel[2] = t0[3];
-        make_window(t0[1], t0[2], halfwidth(t0[3], p.window_sigmas), p.H, p.W, S.win[0]);
+        make_window(t0[1], t0[2], halfwidth(t0[3], p.window_sigmas), p.H, p.W, S.mem[0].win);
         S.nch = 0;
         S.sel_done = (p.max_active <= 1) ? 1 : 0;
     }
     __syncthreads();
     const double a0 = S.t0[0];
-    const int32_t b0 = S.win[0][0], b1 = S.win[0][1], b2 = S.win[0][2], b3 = S.win[0][3];
+    const int32_t b0 = S.mem[0].win[0], b1 = S.mem[0].win[1], b2 = S.mem[0].win[2],
+                  b3 = S.mem[0].win[3];
     const int64_t L = p.st->L;
     constexpr int64_t kSeg = (int64_t)kT * 32;
     for (int64_t top = L; top > 0; top -= kSeg) {
@@ -554,58 +589,80 @@ __device__ inline void out_pair(int o, int n, int &i, int &k)
     k = r + (o - start);
 }
 
-// Orders the LDS accesses of one wave: the lanes of a wave issue LDS
-// instructions together and the LDS serves them in program order, so after
-// this point every lane sees what any lane of the wave wrote before it; the
-// wavefront-scope fences keep the compiler from moving accesses across.
-__device__ __forceinline__ void wave_lds_sync()
+// make_window(x, y, halfwidth(s, ws), ...) in FP64: the bounds are whole
+// numbers, exact there, and need no 64-bit integer conversions.
+__device__ __forceinline__ void window_of(double x, double y, double s, double ws, int64_t H,
+                                          int64_t W, int32_t box[4])
 {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    double h = ceil(ws * s);
+    if (!(h >= 3.0)) h = 3.0;
+    if (h > 1073741823.0) h = 1073741823.0;
+    const double cx = floor(x + 0.5), cy = floor(y + 0.5);
+    const double r0 = cy - h, r1 = cy + h, c0 = cx - h, c1 = cx + h;
+    const double hr = (double)(H - 1), hc = (double)(W - 1);
+    box[0] = (int32_t)(r0 < 0.0 ? 0.0 : r0);
+    box[1] = (int32_t)(r1 > hr ? hr : r1);
+    box[2] = (int32_t)(c0 < 0.0 ? 0.0 : c0);
+    box[3] = (int32_t)(c1 > hc ? hc : c1);
 }
 
-// Member constants at S.th_e, the old members' stored Gaussians at S.th_old
-// and the windows' pixel counts, by the first lanes of wave 0.  A barrier
-// lies between the writes of th_e and this call.
-__device__ __forceinline__ void prepare(const Params &p, WGShared &S)
+// The members' windows at S.th_e and their pixel counts laid end to end, by the
+// first lanes of wave 0 (which wrote th_e, or read it after a barrier).
+__device__ __forceinline__ void prepare_windows(const Params &p, WGShared &S)
 {
     const int t = threadIdx.x;
-    if (t < 64) {
-        const int m = S.m;
-        int64_t area = 0;
-        if (t < m) {
-            const double a = S.th_e[4 * t], x = S.th_e[4 * t + 1], y = S.th_e[4 * t + 2],
-                         s = S.th_e[4 * t + 3];
-            int32_t w[4];
-            make_window(x, y, halfwidth(s, p.window_sigmas), p.H, p.W, w);
-            for (int q = 0; q < 4; ++q) S.win[t][q] = w[q];
-            area = (int64_t)(w[1] - w[0] + 1) * (w[3] - w[2] + 1);
-            const double s2 = s * s;
-            S.mx[t] = x;
-            S.my[t] = y;
-            S.mamp[t] = a;
-            S.minv2[t] = 1.0 / (2.0 * s2);
-            S.minvs2[t] = 1.0 / s2;
-            S.minvs3[t] = 1.0 / (s2 * s);
-            if (t > 0) {
-                const double ox = S.th_old[4 * t + 1], oy = S.th_old[4 * t + 2],
-                             os = S.th_old[4 * t + 3];
-                make_window(ox, oy, halfwidth(os, p.window_sigmas), p.H, p.W, S.wold[t]);
-                S.ox[t] = ox;
-                S.oy[t] = oy;
-                S.oamp[t] = S.th_old[4 * t];
-                S.oinv2[t] = 1.0 / (2.0 * os * os);
-            }
-        }
-        for (int off = 1; off < m; off <<= 1) {
-            const int64_t v = __shfl_up((long long)area, off, 64);
-            if (t >= off) area += v;
-        }
-        if (t < m) S.pref[t + 1] = area;
-        if (t == 0) S.pref[0] = 0;
+    const int m = S.m;
+    int64_t area = 0;
+    if (t < m) {
+        int32_t w[4];
+        window_of(S.th_e[4 * t + 1], S.th_e[4 * t + 2], S.th_e[4 * t + 3], p.window_sigmas, p.H,
+                  p.W, w);
+        Member &M = S.mem[t];
+        for (int q = 0; q < 4; ++q) M.win[q] = w[q];
+        M.wc = w[3] - w[2] + 1;
+        area = (int64_t)(w[1] - w[0] + 1) * (w[3] - w[2] + 1);
     }
-    __syncthreads();
+    for (int off = 1; off < m; off <<= 1) {
+        const int64_t v = __shfl_up((long long)area, off, 64);
+        if (t >= off) area += v;
+    }
+    if (t < m) S.pref[t + 1] = area;
+    if (t == 0) S.pref[0] = 0;
+    wave_lds_sync();
+}
+
+// The members' constants, after the windows.
+__device__ __forceinline__ void prepare_members(WGShared &S)
+{
+    const int t = threadIdx.x;
+    if (t < S.m) {
+        Member &M = S.mem[t];
+        const double s = S.th_e[4 * t + 3], s2 = s * s;
+        M.amp = S.th_e[4 * t];
+        M.x = S.th_e[4 * t + 1];
+        M.y = S.th_e[4 * t + 2];
+        M.inv2 = 1.0 / (2.0 * s2);
+        M.invs2 = 1.0 / s2;
+        M.invs3 = 1.0 / (s2 * s);
+        M.inv_wc = 1.0 / (double)M.wc;
+    }
+    wave_lds_sync();
+}
+
+// The old members' stored Gaussians at S.th_old, once per fit (wave 0).
+__device__ __forceinline__ void prepare_old(const Params &p, WGShared &S)
+{
+    const int t = threadIdx.x;
+    if (t > 0 && t < S.m) {
+        const double ox = S.th_old[4 * t + 1], oy = S.th_old[4 * t + 2], os = S.th_old[4 * t + 3];
+        Stored &O = S.old[t];
+        O.x = ox;
+        O.y = oy;
+        O.amp = S.th_old[4 * t];
+        O.inv2 = 1.0 / (2.0 * os * os);
+        window_of(ox, oy, os, p.window_sigmas, p.H, p.W, O.win);
+    }
+    wave_lds_sync();
 }
 
 __device__ inline double wave_sum(double v)
@@ -614,143 +671,130 @@ __device__ inline double wave_sum(double v)
     return v;
 }
 
-// Tiles tile0, tile0 + stride, ... of U; the work-group's partial (FP64:
-// n_out Gram entries, F, chi2, the pixel count) goes to out.
-__device__ __forceinline__ void evaluate_tiles(const Params &p, WGShared &S, float *tile, double *red,
-                               int64_t tile0, int64_t stride, double *out)
+// in_box without branches between the comparisons (each would wait for its own
+// LDS read).
+__device__ __forceinline__ bool inside(const int32_t b[4], int32_t r, int32_t c)
+{
+    return (r >= b[0]) & (r <= b[1]) & (c >= b[2]) & (c <= b[3]);
+}
+
+// a / d for a < 2^32, 0 < d < 2^32 and inv = 1.0 / d: the FP64 product is off
+// by less than one, so the quotient is it or a neighbour.
+__device__ __forceinline__ uint32_t divide(uint32_t a, uint32_t d, double inv)
+{
+    uint32_t q = (uint32_t)((double)a * inv);
+    const uint32_t lo = q * d;
+    q -= lo > a ? 1u : 0u;
+    q += a - q * d >= d ? 1u : 0u;
+    return q;
+}
+
+// Pixel `lin` of the members' windows laid end to end: its place, whether it is
+// a first occurrence in U, and its residual value.
+struct Pixel {
+    int32_t r, c;
+    bool valid;
+    float rv;
+};
+
+__device__ __forceinline__ Pixel locate(const Params &p, const WGShared &S, int m, int64_t lin,
+                                        int64_t total)
+{
+    Pixel q;
+    q.r = q.c = 0;
+    q.rv = 0.0f;
+    q.valid = lin < total;
+    if (q.valid) {
+        int w = 0;
+        for (int k = 1; k < m; ++k) w += lin >= S.pref[k] ? 1 : 0;
+        // a window lies inside the image (fewer than 2^32 pixels): 32-bit division
+        const Member &M = S.mem[w];
+        const uint32_t local = (uint32_t)(lin - S.pref[w]);
+        const uint32_t wc = (uint32_t)M.wc;
+        const uint32_t dr = divide(local, wc, M.inv_wc);
+        q.r = M.win[0] + (int32_t)dr;
+        q.c = M.win[2] + (int32_t)(local - dr * wc);
+        bool seen = false;
+        for (int i = 0; i < m - 1; ++i) seen |= (i < w) & inside(S.mem[i].win, q.r, q.c);
+        q.valid = !seen;
+        if (q.valid) q.rv = p.R[(int64_t)q.r * p.W + q.c];
+    }
+    return q;
+}
+
+// One pixel of a fit of m members: D, the model M and the row of [J r], which
+// goes through put(column, value), and the sums of M (M - 2 D), (D - M)^2 and
+// the pixels.  Members are taken two at a time: their exponentials (a chain of
+// some 40 dependent FP64 operations each) run side by side, and a window's
+// test selects the result.  A pair that no lane's pixel meets is skipped.
+// The fused multiply-adds are written out (here and in evaluate_tiles_reg), so
+// that every copy the compiler makes of this code rounds alike: a fit of several
+// close members can turn on the last bit of F.
+template <typename Put>
+__device__ __forceinline__ void form_pixel(const WGShared &S, int m, const Pixel &px, Put put,
+                                           double &f_acc, double &c_acc, double &npx)
+{
+    const double cd = (double)px.c, rd = (double)px.r;
+    double D = (double)px.rv;
+    for (int j = 1; j < m; j += 2) {
+        const Stored a = S.old[j], b = S.old[j + 1 < m ? j + 1 : j];
+        const bool ia = px.valid & inside(a.win, px.r, px.c);
+        const bool ib = px.valid & (j + 1 < m) & inside(b.win, px.r, px.c);
+        if (!__any(ia | ib)) continue;
+        const double ax = cd - a.x, ay = rd - a.y, bx = cd - b.x, by = rd - b.y;
+        const double ea = exp(-fma(ax, ax, ay * ay) * a.inv2);
+        const double eb = exp(-fma(bx, bx, by * by) * b.inv2);
+        const double Da = fma(a.amp, ea, D);
+        D = ia ? Da : D;
+        const double Db = fma(b.amp, eb, D);
+        D = ib ? Db : D;
+    }
+    double M = 0.0;
+    for (int j = 0; j < m; j += 2) {
+        const bool two = j + 1 < m;
+        const Member a = S.mem[j], b = S.mem[two ? j + 1 : j];
+        const bool ia = px.valid & inside(a.win, px.r, px.c);
+        const bool ib = px.valid & two & inside(b.win, px.r, px.c);
+        float va[4] = {0.0f, 0.0f, 0.0f, 0.0f}, vb[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+        if (__any(ia | ib)) {
+            const double ax = cd - a.x, ay = rd - a.y, bx = cd - b.x, by = rd - b.y;
+            const double qa = fma(ax, ax, ay * ay), qb = fma(bx, bx, by * by);
+            const double ea = exp(-qa * a.inv2), eb = exp(-qb * b.inv2);
+            const double Ga = a.amp * ea, Gb = b.amp * eb;
+            const double Ma = fma(a.amp, ea, M);
+            M = ia ? Ma : M;
+            const double Mb = fma(b.amp, eb, M);
+            M = ib ? Mb : M;
+            va[0] = ia ? (float)ea : 0.0f;
+            va[1] = ia ? (float)(Ga * ax * a.invs2) : 0.0f;
+            va[2] = ia ? (float)(Ga * ay * a.invs2) : 0.0f;
+            va[3] = ia ? (float)(Ga * qa * a.invs3) : 0.0f;
+            vb[0] = ib ? (float)eb : 0.0f;
+            vb[1] = ib ? (float)(Gb * bx * b.invs2) : 0.0f;
+            vb[2] = ib ? (float)(Gb * by * b.invs2) : 0.0f;
+            vb[3] = ib ? (float)(Gb * qb * b.invs3) : 0.0f;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) put(4 * j + u, va[u]);
+        if (two) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) put(4 * j + 4 + u, vb[u]);
+        }
+    }
+    const double res = D - M;
+    put(4 * m, px.valid ? (float)res : 0.0f);
+    const double fn = fma(M, fma(-2.0, D, M), f_acc), cn = fma(res, res, c_acc);
+    f_acc = px.valid ? fn : f_acc;
+    c_acc = px.valid ? cn : c_acc;
+    npx += px.valid ? 1.0 : 0.0;
+}
+
+// F, chi2 and the pixel count of the work-group into out[0..2]: wave sums, then
+// the four waves in order.
+__device__ __forceinline__ void store_scalars(WGShared &S, double f_acc, double c_acc, double npx,
+                                              double *out)
 {
     const int t = threadIdx.x;
-    const int m = S.m, n = S.n;
-    const int n_out = (n + 1) * (n + 2) / 2;
-    int S_sub = 1, my_s = 0, n_own = 0;
-    int oi[kOwnMax], ok_[kOwnMax];
-    if (n_out <= kT) {
-        S_sub = kT / n_out;
-        my_s = t / n_out;
-        n_own = my_s < S_sub ? 1 : 0;
-        if (n_own) out_pair(t % n_out, n, oi[0], ok_[0]);
-    } else {
-#pragma unroll
-        for (int u = 0; u < kOwnMax; ++u) {
-            const int o = t + u * kT;
-            if (o < n_out) { out_pair(o, n, oi[u], ok_[u]); n_own = u + 1; }
-        }
-    }
-    float acc_s[kOwnMax], acc_c[kOwnMax];
-#pragma unroll
-    for (int u = 0; u < kOwnMax; ++u) { acc_s[u] = 0.0f; acc_c[u] = 0.0f; }
-
-    const int64_t total = S.pref[m];
-    const int64_t ntiles = (total + kT - 1) / kT;
-    double npx = 0.0, f_acc = 0.0, c_acc = 0.0;
-    float *row = tile + t * kTileStride;
-    // This thread's pixel of tile ti: coordinates, whether it is a first
-    // occurrence in U, and its residual value (loaded one tile ahead).
-    auto locate = [&](int64_t ti, int32_t &r, int32_t &c, bool &valid, float &rv) {
-        const int64_t lin = ti * kT + t;
-        valid = false;
-        r = 0;
-        c = 0;
-        rv = 0.0f;
-        if (ti >= ntiles || lin >= total) return;
-        int w = 0;
-        while (lin >= S.pref[w + 1]) ++w;
-        // a window lies inside the image (fewer than 2^32 pixels): 32-bit division
-        const uint32_t local = (uint32_t)(lin - S.pref[w]);
-        const uint32_t wc = (uint32_t)(S.win[w][3] - S.win[w][2] + 1);
-        r = S.win[w][0] + (int32_t)(local / wc);
-        c = S.win[w][2] + (int32_t)(local % wc);
-        valid = true;
-        for (int i = 0; i < w; ++i)
-            if (in_box(S.win[i], r, c)) { valid = false; break; }
-        if (valid) rv = p.R[(int64_t)r * p.W + c];
-    };
-    int32_t nr_, nc_;
-    bool nvalid;
-    float nrv;
-    locate(tile0, nr_, nc_, nvalid, nrv);
-    for (int64_t ti = tile0; ti < ntiles; ti += stride) {
-        const int32_t r = nr_, c = nc_;
-        const bool valid = nvalid;
-        const float rv = nrv;
-        locate(ti + stride, nr_, nc_, nvalid, nrv);
-        if (valid) {
-            npx += 1.0;
-            double D = (double)rv;
-            const double cd = (double)c, rd = (double)r;
-            for (int j = 1; j < m; ++j) {
-                if (!in_box(S.wold[j], r, c)) continue;
-                const double dx = cd - S.ox[j], dy = rd - S.oy[j];
-                D += S.oamp[j] * exp(-(dx * dx + dy * dy) * S.oinv2[j]);
-            }
-            double M = 0.0;
-            for (int j = 0; j < m; ++j) {
-                float *J = row + 4 * j;
-                if (!in_box(S.win[j], r, c)) { J[0] = J[1] = J[2] = J[3] = 0.0f; continue; }
-                const double dx = cd - S.mx[j], dy = rd - S.my[j];
-                const double q = dx * dx + dy * dy;
-                const double e = exp(-q * S.minv2[j]);
-                const double G = S.mamp[j] * e;
-                M += G;
-                J[0] = (float)e;
-                J[1] = (float)(G * dx * S.minvs2[j]);
-                J[2] = (float)(G * dy * S.minvs2[j]);
-                J[3] = (float)(G * q * S.minvs3[j]);
-            }
-            const double res = D - M;
-            row[n] = (float)res;
-            f_acc += M * (M - 2.0 * D);
-            c_acc += res * res;
-        } else {
-            for (int k = 0; k <= n; ++k) row[k] = 0.0f;
-        }
-        __syncthreads();
-        // plain FP32 sum over the tile's pixels, Kahan-compensated across tiles
-#pragma unroll
-        for (int u = 0; u < kOwnMax; ++u) {
-            if (u >= n_own) break;
-            const int ci = oi[u], ck = ok_[u];
-            // four interleaved chains (pixels q, q + S_sub, ... in turn), added
-            // in a fixed order: a quarter of the dependent adds per tile
-            float ts0 = 0.0f, ts1 = 0.0f, ts2 = 0.0f, ts3 = 0.0f;
-            int q = my_s;
-            for (; q + 3 * S_sub < kT; q += 4 * S_sub) {
-                const float *r0 = tile + q * kTileStride, *r1 = r0 + S_sub * kTileStride;
-                const float *r2 = r1 + S_sub * kTileStride, *r3 = r2 + S_sub * kTileStride;
-                ts0 += r0[ci] * r0[ck];
-                ts1 += r1[ci] * r1[ck];
-                ts2 += r2[ci] * r2[ck];
-                ts3 += r3[ci] * r3[ck];
-            }
-            for (; q < kT; q += S_sub) {
-                const float *rq = tile + q * kTileStride;
-                ts0 += rq[ci] * rq[ck];
-            }
-            const float ts = (ts0 + ts1) + (ts2 + ts3);
-            const float y = ts - acc_c[u];
-            const float tt = acc_s[u] + y;
-            acc_c[u] = (tt - acc_s[u]) - y;
-            acc_s[u] = tt;
-        }
-        __syncthreads();
-    }
-    // the work-group's partial, summed over the pixel subsets in a fixed order
-    if (n_out <= kT) {
-        red[t] = n_own ? (double)acc_s[0] - (double)acc_c[0] : 0.0;
-        __syncthreads();
-        if (t < n_out) {
-            double v = 0.0;
-            for (int s = 0; s < S_sub; ++s) v += red[t + s * n_out];
-            out[t] = v;
-        }
-    } else {
-#pragma unroll
-        for (int u = 0; u < kOwnMax; ++u) {
-            if (u >= n_own) break;
-            out[t + u * kT] = (double)acc_s[u] - (double)acc_c[u];
-        }
-    }
-    // F, chi2 and the pixel count: wave sums, then the four waves in order
     const double f_w = wave_sum(f_acc), c_w = wave_sum(c_acc), p_w = wave_sum(npx);
     if ((t & 63) == 0) {
         S.wsum[t >> 6][0] = f_w;
@@ -761,27 +805,92 @@ __device__ __forceinline__ void evaluate_tiles(const Params &p, WGShared &S, flo
     if (t < 3) {
         double v = 0.0;
         for (int w = 0; w < kT / 64; ++w) v += S.wsum[w][t];
-        out[n_out + t] = v;
+        out[t] = v;
     }
     __syncthreads();
 }
 
-// The same partial for fits of three or more members with the Gram sums on
-// the matrix cores.  The tile of [J r] rows is formed in LDS exactly as above.
-// Wave w then takes pixel rows 64w .. 64w+63 of the tile and accumulates
-// G = X^T X over them with v_mfma_f32_16x16x4f32 (four pixels per
-// instruction), one 16 x 16 block per pair of 16-column groups (bi >= bj) of
-// X; columns past n are read as zeros.  A tile's FP32 block sums are added
-// into FP64 accumulators, so the sums across tiles lose nothing.  At the end
-// the four waves' FP64 sums are added through LDS in a fixed order:
-// (w0 + w2) + (w1 + w3).
+// Tiles tile0, tile0 + stride, ... of U for fits of sixteen members; the
+// work-group's partial (FP64: n_out Gram entries, F, chi2, the pixel count)
+// goes to out.  Each thread owns up to kOwnMax Gram entries: a plain FP32 sum
+// over the tile's pixels, Kahan-compensated across tiles.
+__device__ __forceinline__ void evaluate_tiles(const Params &p, WGShared &S, float *tile,
+                                               int64_t tile0, int64_t stride, double *out)
+{
+    const int t = threadIdx.x;
+    const int m = S.m, n = S.n;
+    const int n_out = (n + 1) * (n + 2) / 2;
+    int n_own = 0;
+    int oi[kOwnMax], ok_[kOwnMax];
+#pragma unroll
+    for (int u = 0; u < kOwnMax; ++u) {
+        const int o = t + u * kT;
+        if (o < n_out) { out_pair(o, n, oi[u], ok_[u]); n_own = u + 1; }
+    }
+    float acc_s[kOwnMax], acc_c[kOwnMax];
+#pragma unroll
+    for (int u = 0; u < kOwnMax; ++u) { acc_s[u] = 0.0f; acc_c[u] = 0.0f; }
+
+    const int64_t total = S.pref[m];
+    const int64_t ntiles = (total + kT - 1) / kT;
+    double npx = 0.0, f_acc = 0.0, c_acc = 0.0;
+    float *row = tile + t * kTileStride;
+    Pixel nx = locate(p, S, m, tile0 * kT + t, total);
+    for (int64_t ti = tile0; ti < ntiles; ti += stride) {
+        const Pixel px = nx;
+        nx = locate(p, S, m, (ti + stride) * kT + t, total);   // one tile ahead
+        form_pixel(S, m, px, [&](int c, float v) { row[c] = v; }, f_acc, c_acc, npx);
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < kOwnMax; ++u) {
+            if (u >= n_own) break;
+            const int ci = oi[u], ck = ok_[u];
+            // four interleaved chains (pixels q, q + 4, ... in turn), added in
+            // a fixed order: a quarter of the dependent adds per tile
+            float ts0 = 0.0f, ts1 = 0.0f, ts2 = 0.0f, ts3 = 0.0f;
+            for (int q = 0; q < kT; q += 4) {
+                const float *r0 = tile + q * kTileStride, *r1 = r0 + kTileStride;
+                const float *r2 = r1 + kTileStride, *r3 = r2 + kTileStride;
+                ts0 += r0[ci] * r0[ck];
+                ts1 += r1[ci] * r1[ck];
+                ts2 += r2[ci] * r2[ck];
+                ts3 += r3[ci] * r3[ck];
+            }
+            const float ts = (ts0 + ts1) + (ts2 + ts3);
+            const float y = ts - acc_c[u];
+            const float tt = acc_s[u] + y;
+            acc_c[u] = (tt - acc_s[u]) - y;
+            acc_s[u] = tt;
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int u = 0; u < kOwnMax; ++u) {
+        if (u >= n_own) break;
+        out[t + u * kT] = (double)acc_s[u] - (double)acc_c[u];
+    }
+    store_scalars(S, f_acc, c_acc, npx, out + n_out);
+}
+
+// The same partial for fits of three to fifteen members with the Gram sums on
+// the matrix cores.  Wave w forms its 64 rows of [J r] and keeps them in its
+// own quarter of the tile buffer, column by column, and accumulates G = X^T X
+// over them with v_mfma_f32_16x16x4f32 (four pixels per instruction), one
+// 16 x 16 block per pair of 16-column groups (bi >= bj) of X; columns past n
+// are read as zeros.  A tile's FP32 block sums are added into FP64
+// accumulators, so the sums across tiles lose nothing.  No wave reads another's
+// rows, so a tile costs no barrier; a column is 64 floats at a stride of 68, so
+// that neither the writes (64 pixels of a column) nor the reads (16 columns of
+// 4 pixels) meet in a bank.  At the end the four waves' FP64 sums are added
+// through LDS in a fixed order: (w0 + w2) + (w1 + w3).
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 template <int NB>
-__device__ void evaluate_tiles_mfma(const Params &p, WGShared &S, float *tile, int64_t tile0,
-                                    int64_t stride, double *out)
+__device__ __forceinline__ void evaluate_tiles_mfma(const Params &p, WGShared &S, float *tile,
+                                                    int64_t tile0, int64_t stride, double *out)
 {
-    constexpr int NBL = NB * (NB + 1) / 2;
+    constexpr int NBL = NB * (NB + 1) / 2, XS = 68;
+    static_assert(sizeof(float) * XS * (kMaxN - 3) * (kT / 64) <= kTileBytes, "columns of 15 members");
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
     const int m = S.m, n = S.n, C = n + 1;
     const int n_out = C * (C + 1) / 2;
@@ -794,81 +903,28 @@ __device__ void evaluate_tiles_mfma(const Params &p, WGShared &S, float *tile, i
     const int64_t total = S.pref[m];
     const int64_t ntiles = (total + kT - 1) / kT;
     double npx = 0.0, f_acc = 0.0, c_acc = 0.0;
-    float *row = tile + t * kTileStride;
-    // This thread's pixel of tile ti: coordinates, whether it is a first
-    // occurrence in U, and its residual value (loaded one tile ahead).
-    auto locate = [&](int64_t ti, int32_t &r, int32_t &c, bool &valid, float &rv) {
-        const int64_t lin = ti * kT + t;
-        valid = false;
-        r = 0;
-        c = 0;
-        rv = 0.0f;
-        if (ti >= ntiles || lin >= total) return;
-        int w = 0;
-        while (lin >= S.pref[w + 1]) ++w;
-        // a window lies inside the image (fewer than 2^32 pixels): 32-bit division
-        const uint32_t local = (uint32_t)(lin - S.pref[w]);
-        const uint32_t wc = (uint32_t)(S.win[w][3] - S.win[w][2] + 1);
-        r = S.win[w][0] + (int32_t)(local / wc);
-        c = S.win[w][2] + (int32_t)(local % wc);
-        valid = true;
-        for (int i = 0; i < w; ++i)
-            if (in_box(S.win[i], r, c)) { valid = false; break; }
-        if (valid) rv = p.R[(int64_t)r * p.W + c];
-    };
-    int32_t nr_, nc_;
-    bool nvalid;
-    float nrv;
-    locate(tile0, nr_, nc_, nvalid, nrv);
+    float *xw = tile + wave * (C * XS);
+    float *xput = xw + lane;
     const int kr = lane >> 4, cc = lane & 15;
+    const bool last_in = (NB - 1) * 16 + cc < C;
+    const float *xget = xw + cc * XS + kr;
+    const float *xlast = xw + (last_in ? (NB - 1) * 16 + cc : 0) * XS + kr;
+    Pixel nx = locate(p, S, m, tile0 * kT + t, total);
     for (int64_t ti = tile0; ti < ntiles; ti += stride) {
-        const int32_t r = nr_, c = nc_;
-        const bool valid = nvalid;
-        const float rv = nrv;
-        locate(ti + stride, nr_, nc_, nvalid, nrv);
-        if (valid) {
-            npx += 1.0;
-            double D = (double)rv;
-            const double cd = (double)c, rd = (double)r;
-            for (int j = 1; j < m; ++j) {
-                if (!in_box(S.wold[j], r, c)) continue;
-                const double dx = cd - S.ox[j], dy = rd - S.oy[j];
-                D += S.oamp[j] * exp(-(dx * dx + dy * dy) * S.oinv2[j]);
-            }
-            double M = 0.0;
-            for (int j = 0; j < m; ++j) {
-                float *J = row + 4 * j;
-                if (!in_box(S.win[j], r, c)) { J[0] = J[1] = J[2] = J[3] = 0.0f; continue; }
-                const double dx = cd - S.mx[j], dy = rd - S.my[j];
-                const double q = dx * dx + dy * dy;
-                const double e = exp(-q * S.minv2[j]);
-                const double G = S.mamp[j] * e;
-                M += G;
-                J[0] = (float)e;
-                J[1] = (float)(G * dx * S.minvs2[j]);
-                J[2] = (float)(G * dy * S.minvs2[j]);
-                J[3] = (float)(G * q * S.minvs3[j]);
-            }
-            const double res = D - M;
-            row[n] = (float)res;
-            f_acc += M * (M - 2.0 * D);
-            c_acc += res * res;
-        } else {
-            for (int k = 0; k <= n; ++k) row[k] = 0.0f;
-        }
-        __syncthreads();
+        const Pixel px = nx;
+        nx = locate(p, S, m, (ti + stride) * kT + t, total);   // one tile ahead
+        form_pixel(S, m, px, [&](int c, float v) { xput[c * XS] = v; }, f_acc, c_acc, npx);
+        wave_lds_sync();
         f32x4 acc[NBL];
 #pragma unroll
         for (int q = 0; q < NBL; ++q) acc[q] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll 4
+#pragma unroll
         for (int ks = 0; ks < 16; ++ks) {
-            const float *xr = tile + (wave * 64 + ks * 4 + kr) * kTileStride;
             float x[NB];
 #pragma unroll
-            for (int b = 0; b < NB; ++b) {
-                const int col = b * 16 + cc;
-                x[b] = col < C ? xr[col] : 0.0f;
-            }
+            for (int b = 0; b < NB - 1; ++b) x[b] = xget[b * 16 * XS + 4 * ks];
+            const float xl = xlast[4 * ks];
+            x[NB - 1] = last_in ? xl : 0.0f;
             int q = 0;
 #pragma unroll
             for (int bi = 0; bi < NB; ++bi)
@@ -880,13 +936,14 @@ __device__ void evaluate_tiles_mfma(const Params &p, WGShared &S, float *tile, i
         for (int q = 0; q < NBL; ++q)
 #pragma unroll
             for (int r = 0; r < 4; ++r) g[q][r] += (double)acc[q][r];
-        __syncthreads();                   // the tile is rewritten next
+        wave_lds_sync();                   // the columns are rewritten next
     }
     // Lane l of wave w holds, for block (bi, bj), the entries of rows
     // 16 bi + 4 (l / 16) + r and column 16 bj + l % 16 of G.  Entry (i, k),
     // i <= k, of the output is G[k][i], taken from block (k / 16, i / 16).
     double *buf = reinterpret_cast<double *>(tile);
     static_assert(2 * sizeof(double) * (kMaxN + 1) * (kMaxN + 2) / 2 <= kRowOffset, "wave sums");
+    __syncthreads();                       // every wave's columns are read
     for (int half = 0; half < 2; ++half) {
         if ((wave >> 1) == half) {
             double *dst = buf + (wave & 1) * n_out;
@@ -907,20 +964,7 @@ __device__ void evaluate_tiles_mfma(const Params &p, WGShared &S, float *tile, i
         __syncthreads();
     }
     for (int o = t; o < n_out; o += kT) out[o] = buf[o] + buf[n_out + o];
-    // F, chi2 and the pixel count: wave sums, then the four waves in order
-    const double f_w = wave_sum(f_acc), c_w = wave_sum(c_acc), p_w = wave_sum(npx);
-    if (lane == 0) {
-        S.wsum[wave][0] = f_w;
-        S.wsum[wave][1] = c_w;
-        S.wsum[wave][2] = p_w;
-    }
-    __syncthreads();
-    if (t < 3) {
-        double v = 0.0;
-        for (int w = 0; w < kT / 64; ++w) v += S.wsum[w][t];
-        out[n_out + t] = v;
-    }
-    __syncthreads();
+    store_scalars(S, f_acc, c_acc, npx, out + n_out);
 }
 
 // The same partial for fits of at most two members (n <= 8): each thread keeps
@@ -928,111 +972,160 @@ __device__ void evaluate_tiles_mfma(const Params &p, WGShared &S, float *tile, i
 // tile.  J and r are FP32 values; their products are exact in FP64 and are
 // accumulated there (one FP64 FMA per entry, half the work of a Kahan update
 // in FP32 on this hardware and a smaller error).  The threads' sums are
-// combined once at the end by wave shuffles and the four waves in order.
+// combined once at the end through LDS and the four waves in order.
+//
+// With one wave per SIMD the loop is a chain of latencies (the residual's
+// load, then an exponential of some 40 dependent FP64 operations), so a thread
+// takes two tiles side by side, without branches between them, and loads the
+// residual of the next two before it starts: the sums still add the tiles in
+// order.
 template <int M>
 __device__ __forceinline__ void evaluate_tiles_reg(const Params &p, WGShared &S, int64_t tile0, int64_t stride,
                                    double *out, float *stage)
 {
     constexpr int N = 4 * M, C = N + 1, NO = C * (C + 1) / 2;
     const int t = threadIdx.x;
-    const int64_t total = S.pref[M];
+    const int64_t total = S.pref[M], first = S.pref[1];
     const int64_t ntiles = (total + kT - 1) / kT;
-    // This thread's pixel of tile ti (row-major within the window it falls in).
-    auto locate = [&](int64_t lin, int &w, int32_t &r, int32_t &c) {
-        w = (M > 1 && lin >= S.pref[1]) ? 1 : 0;
-        // a window lies inside the image (fewer than 2^32 pixels): 32-bit division
-        const uint32_t local = (uint32_t)(lin - S.pref[w]);
-        const uint32_t wc = (uint32_t)(S.win[w][3] - S.win[w][2] + 1);
-        r = S.win[w][0] + (int32_t)(local / wc);
-        c = S.win[w][2] + (int32_t)(local % wc);
+    Member mem[M];
+#pragma unroll
+    for (int j = 0; j < M; ++j) mem[j] = S.mem[j];
+    Stored old = {};
+    if (M > 1) old = S.old[1];
+    struct Px { int32_t r, c; bool valid, in0; float rv; };
+    // This thread's pixel of tile ti (row-major within the window it falls in),
+    // whether it is a first occurrence in U, and its residual value.
+    auto place = [&](int64_t ti) {
+        Px q;
+        const int64_t lin = ti * kT + t;
+        q.r = q.c = 0;
+        q.in0 = true;
+        q.rv = 0.0f;
+        q.valid = lin < total;             // ti >= ntiles implies lin >= total
+        if (q.valid) {
+            const bool second = M > 1 && lin >= first;
+            // a window lies inside the image (fewer than 2^32 pixels): 32-bit division
+            const uint32_t local = (uint32_t)(lin - (second ? first : 0));
+            const uint32_t wc = (uint32_t)(second ? mem[M - 1].wc : mem[0].wc);
+            const uint32_t dr = divide(local, wc, second ? mem[M - 1].inv_wc : mem[0].inv_wc);
+            q.r = (second ? mem[M - 1].win[0] : mem[0].win[0]) + (int32_t)dr;
+            q.c = (second ? mem[M - 1].win[2] : mem[0].win[2]) + (int32_t)(local - dr * wc);
+            q.in0 = !second;
+            if (M > 1) q.valid = !(second & inside(mem[0].win, q.r, q.c));
+            if (q.valid) q.rv = p.R[(int64_t)q.r * p.W + q.c];
+        }
+        return q;
     };
     double acc[NO];
 #pragma unroll
     for (int o = 0; o < NO; ++o) acc[o] = 0.0;
     double npx = 0.0, f_acc = 0.0, c_acc = 0.0;
-    for (int64_t ti = tile0; ti < ntiles; ti += stride) {
-        const int64_t lin = ti * kT + t;
-        if (lin >= total) continue;
-        int w;
-        int32_t r, c;
-        locate(lin, w, r, c);
-        if (M > 1 && w == 1 && in_box(S.win[0], r, c)) continue;
-        npx += 1.0;
-        double D = (double)p.R[(int64_t)r * p.W + c];
-        const double cd = (double)c, rd = (double)r;
-        if (M > 1 && in_box(S.wold[1], r, c)) {
-            const double dx = cd - S.ox[1], dy = rd - S.oy[1];
-            D += S.oamp[1] * exp(-(dx * dx + dy * dy) * S.oinv2[1]);
+    struct Cols { float col[C]; double D, Mv, res; };
+    // D, the model and the row of [J r] of one pixel; a window's test selects
+    // the result, so that two pixels run side by side
+    auto form = [&](const Px &q, Cols &o) {
+        double D = (double)q.rv;
+        const double cd = (double)q.c, rd = (double)q.r;
+        if (M > 1) {
+            const bool in = inside(old.win, q.r, q.c);
+            const double dx = cd - old.x, dy = rd - old.y;
+            const double Dn = fma(old.amp, exp(-fma(dy, dy, dx * dx) * old.inv2), D);
+            D = in ? Dn : D;
         }
-        float col[C];
         double Mv = 0.0;
 #pragma unroll
         for (int j = 0; j < M; ++j) {
-            if (!in_box(S.win[j], r, c)) {
-                col[4 * j] = col[4 * j + 1] = col[4 * j + 2] = col[4 * j + 3] = 0.0f;
-                continue;
-            }
-            const double dx = cd - S.mx[j], dy = rd - S.my[j];
-            const double q = dx * dx + dy * dy;
-            const double e = exp(-q * S.minv2[j]);
-            const double G = S.mamp[j] * e;
-            Mv += G;
-            col[4 * j] = (float)e;
-            col[4 * j + 1] = (float)(G * dx * S.minvs2[j]);
-            col[4 * j + 2] = (float)(G * dy * S.minvs2[j]);
-            col[4 * j + 3] = (float)(G * q * S.minvs3[j]);
+            // a pixel is listed by the first window that holds it
+            const bool in = j == 0 ? q.in0 : (!q.in0 | inside(mem[j].win, q.r, q.c));
+            const double dx = cd - mem[j].x, dy = rd - mem[j].y;
+            const double qq = fma(dy, dy, dx * dx);
+            const double e = exp(-qq * mem[j].inv2);
+            const double G = mem[j].amp * e;
+            const double Mn = fma(mem[j].amp, e, Mv);
+            Mv = in ? Mn : Mv;
+            const bool use = in & q.valid;
+            o.col[4 * j] = use ? (float)e : 0.0f;
+            o.col[4 * j + 1] = use ? (float)(G * dx * mem[j].invs2) : 0.0f;
+            o.col[4 * j + 2] = use ? (float)(G * dy * mem[j].invs2) : 0.0f;
+            o.col[4 * j + 3] = use ? (float)(G * qq * mem[j].invs3) : 0.0f;
         }
-        const double res = D - Mv;
-        col[N] = (float)res;
-        f_acc += Mv * (Mv - 2.0 * D);
-        c_acc += res * res;
+        o.D = D;
+        o.Mv = Mv;
+        o.res = D - Mv;
+        o.col[N] = q.valid ? (float)o.res : 0.0f;
+    };
+    auto add = [&](const Px &q, const Cols &o) {
+        const double fn = fma(o.Mv, fma(-2.0, o.D, o.Mv), f_acc), cn = fma(o.res, o.res, c_acc);
+        f_acc = q.valid ? fn : f_acc;
+        c_acc = q.valid ? cn : c_acc;
+        npx += q.valid ? 1.0 : 0.0;
         double cold[C];
 #pragma unroll
-        for (int i = 0; i < C; ++i) cold[i] = (double)col[i];
-        int o = 0;
+        for (int i = 0; i < C; ++i) cold[i] = (double)o.col[i];
+        int e = 0;
 #pragma unroll
         for (int i = 0; i < C; ++i)
 #pragma unroll
-            for (int k = i; k < C; ++k, ++o) acc[o] = fma(cold[i], cold[k], acc[o]);
+            for (int k = i; k < C; ++k, ++e) acc[e] = fma(cold[i], cold[k], acc[e]);
+    };
+    Px a = place(tile0), b = place(tile0 + stride);
+    for (int64_t ti = tile0; ti < ntiles; ti += 2 * stride) {
+        Px na = a, nb = b;
+        if (ti + 2 * stride < ntiles) {
+            na = place(ti + 2 * stride);
+            nb = place(ti + 3 * stride);
+        }
+        Cols ca, cb;
+        form(a, ca);
+        form(b, cb);
+        add(a, ca);
+        add(b, cb);
+        a = na;
+        b = nb;
     }
     const int lane = t & 63, wave = t >> 6;
     // Wave sums of the Gram entries, F, chi2 and the pixel count, through the
-    // tile buffer (idle in this path): each wave writes its lanes' values,
-    // half of them at a time, and lane q then adds value q over the 64 lanes
-    // in lane order.  Rows are padded to 65 doubles against bank conflicts.
-    constexpr int NV = NO + 3, HALF = (NV + 1) / 2, ROW = 65;
-    static_assert(sizeof(double) * (kT / 64) * HALF * ROW <= kRowOffset, "reduction buffer");
+    // tile buffer (idle in this path), CH values at a time: each wave writes
+    // its lanes' values; then lane (q, c) adds value q over lanes 16 c ..
+    // 16 c + 15 in order, 16 values by all lanes and the rest by the first
+    // lanes.  The four chains of the four waves meet at the end: (0 + 1) +
+    // (2 + 3) of a wave, then the waves in order.  Rows are padded to 65
+    // doubles, so the 32 lanes served together read 32 different bank pairs.
+    constexpr int NV = NO + 3, CH = M == 1 ? 18 : 24, ROW = 65, REST = CH - 16;
+    static_assert(NV % CH == 0 && REST > 0 && REST <= 8, "chunks of 17 .. 24 values");
+    static_assert(sizeof(double) * (kT / 64) * CH * ROW <= kRowOffset, "reduction buffer");
     double v[NV];
 #pragma unroll
     for (int o = 0; o < NO; ++o) v[o] = acc[o];
     v[NO] = f_acc;
     v[NO + 1] = c_acc;
     v[NO + 2] = npx;
-    double *buf = reinterpret_cast<double *>(stage) + wave * (HALF * ROW);
+    double *buf = reinterpret_cast<double *>(stage) + wave * (CH * ROW);
+    const int qa = lane & 15, va = lane >> 4;
+    const int qb = 16 + (lane & 7), vb = (lane >> 3) & 3;
+    const bool has_b = lane < 32 && qb < CH;
+    const double *ra = buf + qa * ROW + 16 * va, *rb = buf + (has_b ? qb : 0) * ROW + 16 * vb;
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
+    for (int h = 0; h < NV / CH; ++h) {
+        if (h > 0) wave_lds_sync();        // the buffer has been read
 #pragma unroll
-        for (int q = 0; q < HALF; ++q)
-            if (h * HALF + q < NV) buf[q * ROW + lane] = v[h * HALF + q];
+        for (int q = 0; q < CH; ++q) buf[q * ROW + lane] = v[h * CH + q];
         wave_lds_sync();
-        if (lane < HALF && h * HALF + lane < NV) {
-            // four interleaved chains over the lanes, added in a fixed order
-            const double *row = buf + lane * ROW;
-            double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
-            for (int l = 0; l < 16; ++l) {
-                s0 += row[l];
-                s1 += row[l + 16];
-                s2 += row[l + 32];
-                s3 += row[l + 48];
-            }
-            S.wred[wave][h * HALF + lane] = (s0 + s1) + (s2 + s3);
+        double sa = 0.0, sb = 0.0;
+#pragma unroll
+        for (int l = 0; l < 16; ++l) {
+            sa += ra[l];
+            sb += rb[l];
         }
-        wave_lds_sync();                   // the buffer is rewritten by the next half
+        S.wred[wave][va][h * CH + qa] = sa;
+        if (has_b) S.wred[wave][vb][h * CH + qb] = sb;
     }
     __syncthreads();
-    if (t < NO + 3) {
+    if (t < NV) {
         double tot = 0.0;
-        for (int wv = 0; wv < kT / 64; ++wv) tot += S.wred[wv][t];
+#pragma unroll
+        for (int w = 0; w < kT / 64; ++w)
+            tot += (S.wred[w][0][t] + S.wred[w][1][t]) + (S.wred[w][2][t] + S.wred[w][3][t]);
         out[t] = tot;
     }
     __syncthreads();
@@ -1045,11 +1138,15 @@ __device__ __forceinline__ double sum_column(const Params &p, int w0, int w1, in
     for (int w = w0; w < w1; w += 16) {
         double a[16];
 #pragma unroll
-        for (int u = 0; u < 16; ++u)
-            a[u] = w + u < w1 ? ld_shared(p.partials + (int64_t)(w + u) * kPartStride + o) : 0.0;
+        for (int u = 0; u < 16; ++u) {
+            const int r = w + u < w1 ? w + u : w1 - 1;   // rows past the last: read, not added
+            a[u] = ld_shared(p.partials + (int64_t)r * kPartStride + o);
+        }
 #pragma unroll
-        for (int u = 0; u < 16; ++u)
-            if (w + u < w1) v += a[u];
+        for (int u = 0; u < 16; ++u) {
+            const double s = v + a[u];
+            v = w + u < w1 ? s : v;
+        }
     }
     return v;
 }
@@ -1079,71 +1176,6 @@ __device__ __forceinline__ void reduce_partials(const Params &p, WGShared &S, in
     __syncthreads();
 }
 
-// The same of a trial the leader evaluated alone (its row in LDS).
-__device__ __forceinline__ void reduce_own(WGShared &S, const double *row, double *He)
-{
-    const int n = S.n, nv = (n + 1) * (n + 2) / 2 + 3;
-    for (int o = threadIdx.x; o < nv; o += kT) put_sum(S, He, n, o, 0.0 + row[o]);
-    __syncthreads();
-}
-
-// Work-group Cholesky solve of A x = b (A n x n in LDS, overwritten; b
-// overwritten), n <= 64, in the textbook arithmetic: L_kk = sqrt(d_k),
-// L_ik = A_ik / L_kk, A_ij -= L_ik L_jk, then the two triangular solves with
-// divisions by L_kk.  Column k of L is written into row k of the upper
-// triangle (U[k][i] = L[i][k]); the diagonal keeps the pivots d_k and the
-// L_kk go to S.ldiag.  Every thread takes the square root itself, so a column
-// costs two barriers (after the scaled column, after the trailing update,
-// which the threads share as a 16 x 16 grid).  The triangular solves run on
-// wave 0, one lane per row, with no barrier.
-__device__ bool chol_solve(WGShared &S, double *A, int n, double *b, double *x)
-{
-    static_assert(kMaxN <= 64, "one lane per row in the triangular solves");
-    static_assert(kT == 256, "a 16 x 16 thread grid");
-    const int t = threadIdx.x, ti = t >> 4, tj = t & 15;
-    for (int k = 0; k < n; ++k) {
-        const double d = A[k * n + k];
-        if (!(d > 0.0 && isfinite(d))) return false;     // the same for every thread
-        const double l = sqrt(d);
-        for (int i = k + 1 + t; i < n; i += kT) A[k * n + i] = A[i * n + k] / l;
-        if (t == 0) S.ldiag[k] = l;
-        __syncthreads();
-        const double *Lk = A + k * n;                    // L[i][k] = Lk[i], i > k
-        for (int i = k + 1 + ti; i < n; i += 16) {
-            const double lik = Lk[i];
-            for (int j = k + 1 + tj; j <= i; j += 16) A[i * n + j] -= lik * Lk[j];
-        }
-        __syncthreads();
-    }
-    if (t < 64) {
-        const int lane = t;
-        // L y = b, with L[j][i] = A[i][j] for j > i
-        for (int i = 0; i < n; ++i) {
-            wave_lds_sync();
-            const double yi = b[i] / S.ldiag[i];
-            const int j = i + 1 + lane;
-            if (j < n) b[j] -= A[i * n + j] * yi;
-            if (lane == 0) x[i] = yi;
-        }
-        // L^T x = y, with L[i][j] = A[j][i] for j < i
-        for (int i = n - 1; i >= 0; --i) {
-            wave_lds_sync();
-            const double xi = x[i] / S.ldiag[i];
-            wave_lds_sync();                 // x[i] is read by every lane before it is rewritten
-            if (lane == 0) x[i] = xi;
-            for (int j = lane; j < i; j += 64) x[j] -= A[j * n + i] * xi;
-        }
-        wave_lds_sync();
-        if (lane == 0) {
-            int good = 1;
-            for (int i = 0; i < n; ++i) good &= isfinite(x[i]) ? 1 : 0;
-            S.ok = good;
-        }
-    }
-    __syncthreads();
-    return S.ok != 0;
-}
-
 // ---------------------------------------------------------------------------
 // The LM bookkeeping (Marquardt 1963) after one evaluation, work-group 0.
 // Damped system (H + mu D) delta = g with D = diag(max(H_ii, 1e-12 max
@@ -1156,103 +1188,167 @@ __device__ bool chol_solve(WGShared &S, double *A, int n, double *b, double *x)
 // holds the next trial point.
 // ---------------------------------------------------------------------------
 
-// Acceptance of the evaluated trial and the damping update (thread 0).
+// Lane l's value in every lane (l the same for all lanes).
+__device__ __forceinline__ double lane_value(double v, int l)
+{
+    const int lo = __builtin_amdgcn_readlane(__double2loint(v), l);
+    const int hi = __builtin_amdgcn_readlane(__double2hiint(v), l);
+    return __hiloint2double(hi, lo);
+}
+
+// The largest of the lanes' values, none below 0 (a NaN counts as 0).
+__device__ __forceinline__ double wave_max0(double v)
+{
+    v = v > 0.0 ? v : 0.0;
+    for (int off = 32; off > 0; off >>= 1) {
+        const double o = __shfl_xor(v, off, 64);
+        v = o > v ? o : v;
+    }
+    return v;
+}
+
+// Acceptance of the evaluated trial and the damping update, by wave 0.  The
+// relative step of parameter i is lane i's.
 __device__ __forceinline__ void lm_accept(const Params &p, WGShared &S)
 {
-    const int m = S.m;
-    S.finished = 0;
-    if (S.phase == 0) {
-        S.accept = 1;
-        S.mu = p.lm_mu0;
-        S.nu = 2.0;
-        S.trials = 0;
-        S.converged = 0;
-        S.chi2_init = S.chi2e;
-        S.phase = S.alt_pending ? 2 : 1;
-        return;
-    }
-    if (S.phase == 2) {
-        // the proposal against the simple start: the lower objective is the
-        // start of LM; the damping is untouched
-        double Fp = S.Fe;
-        if (!isfinite(Fp)) Fp = INFINITY;
-        S.accept = (Fp < S.F_c) ? 1 : 0;
-        S.chose_prop = S.accept;
-        if (S.accept) {
-            S.chi2_init = S.chi2e;
-            for (int i = 0; i < 4; ++i) S.th0[i] = S.th_e[i];
-        }
-        S.phase = 1;
-        return;
-    }
+    const int t = threadIdx.x, n = S.n;
+    const int phase = S.phase;
     double Ft = S.Fe;
     if (!isfinite(Ft)) Ft = INFINITY;
-    S.accept = (Ft < S.F_c) ? 1 : 0;
-    if (S.accept) {
-        double step = 0.0;
-        for (int j = 0; j < m; ++j) {
-            const double *tn = S.th_e + 4 * j, *to = S.th_c + 4 * j;
-            const double sa = fabs(tn[0]) > 1e-30 ? fabs(tn[0]) : 1e-30;
-            double v;
-            v = fabs(tn[0] - to[0]) / sa; step = v > step ? v : step;
-            v = fabs(tn[1] - to[1]) / tn[3]; step = v > step ? v : step;
-            v = fabs(tn[2] - to[2]) / tn[3]; step = v > step ? v : step;
-            v = fabs(tn[3] - to[3]) / tn[3]; step = v > step ? v : step;
+    const double F_c = S.F_c, chi2e = S.chi2e;
+    const bool better = Ft < F_c;
+    const bool accept = phase == 0 || better;
+    if (phase != 1) {
+        if (t == 0) {
+            S.finished = 0;
+            S.accept = accept ? 1 : 0;
+            if (phase == 0) {
+                S.mu = p.lm_mu0;
+                S.nu = 2.0;
+                S.trials = 0;
+                S.converged = 0;
+                S.chi2_init = chi2e;
+                S.phase = S.alt_pending ? 2 : 1;
+            } else {
+                // the proposal against the simple start: the lower objective is
+                // the start of LM; the damping is untouched
+                S.chose_prop = S.accept;
+                if (accept) {
+                    S.chi2_init = chi2e;
+                    for (int i = 0; i < 4; ++i) S.th0[i] = S.th_e[i];
+                }
+                S.phase = 1;
+            }
         }
-        const double rho = S.pred > 0.0 ? (S.F_c - Ft) / S.pred : 1.0;
+    } else if (accept) {
+        // the step relative to the trial's amplitude or width
+        double v = 0.0;
+        if (t < n) {
+            const double tn = S.th_e[t], w = S.th_e[t | 3];
+            const double sa = fabs(tn) > 1e-30 ? fabs(tn) : 1e-30;
+            v = fabs(tn - S.th_c[t]) / ((t & 3) == 0 ? sa : w);
+        }
+        const double pred = S.pred;
+        const double rho = pred > 0.0 ? (F_c - Ft) / pred : 1.0;
         const double tt = 2.0 * rho - 1.0;
         double f = 1.0 - tt * tt * tt;
         if (f < 1.0 / 3.0) f = 1.0 / 3.0;
-        S.mu *= f;
-        if (S.mu < 1e-12) S.mu = 1e-12;
-        S.nu = 2.0;
-        if (step < p.lm_tol) { S.converged = 1; S.finished = 1; }
-    } else {
+        double mu = S.mu * f;
+        if (mu < 1e-12) mu = 1e-12;
+        const bool end = !__any(!(v < p.lm_tol) && v == v);
+        if (t == 0) {
+            S.accept = 1;
+            S.mu = mu;
+            S.nu = 2.0;
+            S.finished = 0;
+            if (end) { S.converged = 1; S.finished = 1; }
+        }
+    } else if (t == 0) {
+        S.accept = 0;
+        S.finished = 0;
         S.mu *= S.nu;
         S.nu *= 2.0;
         if (S.mu > 1e8) { S.converged = 1; S.finished = 1; }
     }
+    // the evaluated point becomes the current one; its Gram matrix buffer
+    // becomes the current buffer (no copy)
+    if (accept) {
+        if (t < n) { S.th_c[t] = S.th_e[t]; S.g_c[t] = S.ge[t]; }
+        if (t == 0) {
+            S.F_c = S.Fe; S.chi2_c = chi2e; S.npx_c = S.npx_e;
+            S.hsel ^= 1;
+        }
+    }
+    wave_lds_sync();
 }
 
-// The damped solve for n = N <= 8 by thread 0 alone, the factor's lower
-// triangle in registers: the same arithmetic as the work-group path below,
-// with each Cholesky column scaled by one reciprocal square root.
+// h + mu d with the product rounded on its own (not fused).
+__device__ __forceinline__ double damped(double h, double mu, double d)
+{
+#pragma clang fp contract(off)
+    const double q = mu * d;
+    return h + q;
+}
+
+// The damped solve for n = N <= 8 by wave 0: every lane holds the factor's
+// lower triangle and does the same arithmetic (each Cholesky column scaled by
+// one reciprocal square root), so that nothing crosses lanes on the way; the
+// per-parameter steps around it (bounds, clipping, the store) are one lane per
+// parameter.  The chain is a square root, a division and two multiply-adds per
+// column, about 260 clocks.
 template <int N>
 __device__ __forceinline__ void lm_solve_small(int32_t lm_max_iter, WGShared &S, const double *Hc)
 {
+    const int t = threadIdx.x;            // lane of wave 0
+    const int q = t < N ? t : 0;          // its parameter
+    const double th = S.th_c[q], g = S.g_c[q], lo = S.lo[q], hi = S.hi[q];
+    double h[N][N];
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+#pragma unroll
+        for (int k = 0; k <= i; ++k) h[i][k] = Hc[i * N + k];
+    double rhs[N], dd[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) rhs[i] = S.g_c[i];
+    const bool fr = (th <= lo && g <= 0.0) || (th >= hi && g >= 0.0);
+    const unsigned int frozen = (unsigned int)__ballot(fr && t < N);
+    double mu = S.mu, nu = S.nu;
+    int trials = S.trials, finished = S.finished, converged = S.converged;
     double dmax = 0.0;
 #pragma unroll
-    for (int i = 0; i < N; ++i) dmax = Hc[i * N + i] > dmax ? Hc[i * N + i] : dmax;
-    double dd[N], rhs[N];
-    bool fr[N];
+    for (int i = 0; i < N; ++i) dmax = h[i][i] > dmax ? h[i][i] : dmax;
+    const double dmin = 1e-12 * dmax;
 #pragma unroll
-    for (int i = 0; i < N; ++i) {
-        const double hii = Hc[i * N + i];
-        dd[i] = hii < 1e-12 * dmax ? 1e-12 * dmax : hii;
-        const double th = S.th_c[i], g = S.g_c[i];
-        fr[i] = (th <= S.lo[i] && g <= 0.0) || (th >= S.hi[i] && g >= 0.0);
-        rhs[i] = fr[i] ? 0.0 : g;
+    for (int i = 0; i < N; ++i) dd[i] = h[i][i] < dmin ? dmin : h[i][i];
+    if (frozen) {
+        // a parameter held on its bound: an identity row and column
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            const bool fi = (frozen >> i) & 1u;
+            rhs[i] = fi ? 0.0 : rhs[i];
+#pragma unroll
+            for (int k = 0; k < i; ++k) h[i][k] = (fi || ((frozen >> k) & 1u)) ? 0.0 : h[i][k];
+        }
     }
-    while (!S.finished) {
-        if (S.trials >= lm_max_iter) { S.finished = 1; break; }
-        S.trials++;
-        const double mu = S.mu;
+    while (!uniform(finished != 0)) {
+        if (uniform(trials >= lm_max_iter)) { finished = 1; break; }
+        trials++;
         double a[N][N];
 #pragma unroll
-        for (int i = 0; i < N; ++i)
+        for (int i = 0; i < N; ++i) {
 #pragma unroll
-            for (int k = 0; k <= i; ++k)
-                a[i][k] = (fr[i] || fr[k]) ? (i == k ? 1.0 : 0.0)
-                                           : Hc[i * N + k] + (i == k ? mu * dd[i] : 0.0);
+            for (int k = 0; k < i; ++k) a[i][k] = h[i][k];
+            const double v = fma(mu, dd[i], h[i][i]);
+            a[i][i] = ((frozen >> i) & 1u) ? 1.0 : v;
+        }
         bool ok = true;
         double rinv[N];                  // 1 / L_kk
 #pragma unroll
         for (int k = 0; k < N; ++k) {
             const double d = a[k][k];
             ok = ok && d > 0.0 && isfinite(d);
-            const double r = ok ? 1.0 / sqrt(d) : 0.0;
+            const double r = 1.0 / sqrt(d);
             rinv[k] = r;
-            a[k][k] = ok ? d * r : 1.0;
 #pragma unroll
             for (int i = k + 1; i < N; ++i) a[i][k] *= r;
 #pragma unroll
@@ -1261,62 +1357,161 @@ __device__ __forceinline__ void lm_solve_small(int32_t lm_max_iter, WGShared &S,
                 for (int j = k + 1; j <= i; ++j) a[i][j] -= a[i][k] * a[j][k];
         }
         double x[N];
-        if (ok) {
 #pragma unroll
-            for (int i = 0; i < N; ++i) {
-                double v = rhs[i];
+        for (int i = 0; i < N; ++i) {
+            double v = rhs[i];
 #pragma unroll
-                for (int j = 0; j < i; ++j) v -= a[i][j] * x[j];
-                x[i] = v * rinv[i];
-            }
-#pragma unroll
-            for (int i = N - 1; i >= 0; --i) {
-                double v = x[i];
-#pragma unroll
-                for (int j = i + 1; j < N; ++j) v -= a[j][i] * x[j];
-                x[i] = v * rinv[i];
-            }
-#pragma unroll
-            for (int i = 0; i < N; ++i) ok = ok && isfinite(x[i]);
+            for (int j = 0; j < i; ++j) v -= a[i][j] * x[j];
+            x[i] = v * rinv[i];
         }
-        if (ok) {
+#pragma unroll
+        for (int i = N - 1; i >= 0; --i) {
+            double v = x[i];
+#pragma unroll
+            for (int j = i + 1; j < N; ++j) v -= a[j][i] * x[j];
+            x[i] = v * rinv[i];
+        }
+#pragma unroll
+        for (int i = 0; i < N; ++i) ok = ok && isfinite(x[i]);
+        if (uniform(ok)) {
+            double xi = x[0];
+#pragma unroll
+            for (int k = 1; k < N; ++k) xi = q == k ? x[k] : xi;
+            double v = th + xi;
+            if (!(v >= lo)) v = lo;
+            if (v > hi) v = hi;
+            if (t < N) S.th_e[t] = v;
             double pred = 0.0;
 #pragma unroll
-            for (int i = 0; i < N; ++i) {
-                double v = S.th_c[i] + x[i];
-                if (!(v >= S.lo[i])) v = S.lo[i];
-                if (v > S.hi[i]) v = S.hi[i];
-                S.th_e[i] = v;
-                S.delta[i] = x[i];
-                pred += x[i] * (rhs[i] + mu * dd[i] * x[i]);
-            }
-            S.pred = pred;
+            for (int i = 0; i < N; ++i) pred += x[i] * (rhs[i] + mu * dd[i] * x[i]);
+            if (t == 0) S.pred = pred;
             break;
         }
         // not positive definite: treated as a rejected trial
-        S.mu *= S.nu;
-        S.nu *= 2.0;
-        if (S.mu > 1e8) { S.converged = 1; S.finished = 1; }
+        mu *= nu;
+        nu *= 2.0;
+        if (mu > 1e8) { converged = 1; finished = 1; }
+    }
+    if (t == 0) {
+        S.mu = mu;
+        S.nu = nu;
+        S.trials = trials;
+        S.finished = finished;
+        S.converged = converged;
     }
 }
 
-__device__ __forceinline__ void lm_step(const Params &p, WGShared &S, double *H2, double *A)
+// Cholesky factor of A and the solution of L y = b (n < 64: b takes the place of
+// row 0, which has no entry below the diagonal; n = 64: without b), in the
+// textbook arithmetic: L_kk = sqrt(d_k), L_ik = A_ik / L_kk,
+// A_ij -= L_ik L_jk.  Lane i of wave w keeps the entries of row i in the
+// columns w, w + 4, ... w + 4 (V - 1) in registers.  The owner of column k scales it (one
+// square root, one division per lane) and writes it to row k of Lt; after one
+// barrier every wave updates its own columns from there, uniform reads of L_jk
+// and one of L_ik.  Entries above the diagonal and of finished columns are
+// carried along unread, so a column has no conditions.  Lt[k][i] = L_ik for
+// i > k, y_k at i = 0; the L_kk go to S.ldiag.  S.pd is cleared when A is not
+// positive definite.
+constexpr int kLtStride = kMaxN + 2;
+template <int V>
+__device__ __forceinline__ void chol_factor(WGShared &S, const double *Hc, int n, double mu, double *Lt)
 {
-    const int t = threadIdx.x;
-    const int n = S.n;
-    if (t == 0) lm_accept(p, S);
-    __syncthreads();
-    if (S.accept) {
-        // the evaluated point becomes the current one; its Gram matrix buffer
-        // becomes the current buffer (no copy)
-        if (t < n) { S.th_c[t] = S.th_e[t]; S.g_c[t] = S.ge[t]; }
-        if (t == 0) {
-            S.F_c = S.Fe; S.chi2_c = S.chi2e; S.npx_c = S.npx_e;
-            S.hsel ^= 1;
+    static_assert(kT == 256 && kMaxN <= 64, "four waves, one lane per row");
+    static_assert(sizeof(double) * (size_t)kMaxN * kLtStride <= kTileBytes, "L in the tile buffer");
+    const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    double a[V];
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+        const int j = wave + 4 * v;
+        double x = 0.0;
+        if (j < n) {
+            if (lane == 0) x = n == kMaxN ? 0.0 : S.rhs[j];
+            else if (lane == j) x = S.frozen[j] ? 1.0 : damped(Hc[j * n + j], mu, S.dd[j]);
+            else if (lane < n && !(S.frozen[lane] || S.frozen[j])) x = Hc[j * n + lane];   // symmetric
+        }
+        a[v] = x;
+    }
+    // the first pivot has no lane of its own
+    const double d0 = S.frozen[0] ? 1.0 : damped(Hc[0], mu, S.dd[0]);
+#pragma unroll
+    for (int vk = 0; vk < V; ++vk) {
+        if (4 * vk >= n) break;
+#pragma unroll 1
+        for (int w = 0; w < 4; ++w) {
+            const int k = 4 * vk + w;            // n is a multiple of 4
+            double *Lk = Lt + k * kLtStride;
+            if (wave == w) {
+                const double d = k == 0 ? d0 : lane_value(a[vk], k);
+                const double l = sqrt(d);
+                Lk[lane] = a[vk] / l;
+                if (lane == 0) {
+                    S.ldiag[k] = l;
+                    if (!(d > 0.0 && isfinite(d))) S.pd = 0;
+                }
+            }
+            __syncthreads();
+            const double li = Lk[lane];
+            double lj[V];
+#pragma unroll
+            for (int v = vk; v < V; ++v) lj[v] = Lk[wave + 4 * v];
+#pragma unroll
+            for (int v = vk; v < V; ++v) a[v] -= li * lj[v];
         }
     }
+}
+
+// The damped solve for n > 8: the factorisation above, then L^T x = y by wave
+// 0, one lane per row.
+__device__ __forceinline__ bool chol_solve(WGShared &S, const double *Hc, int n, double mu, double *Lt)
+{
+    const int t = threadIdx.x;
+    if (t == 0) S.pd = 1;
+    if (n <= 16) chol_factor<4>(S, Hc, n, mu, Lt);
+    else if (n <= 32) chol_factor<8>(S, Hc, n, mu, Lt);
+    else chol_factor<kMaxN / 4>(S, Hc, n, mu, Lt);
     __syncthreads();
-    if (S.phase == 2) {
+    if (t < 64) {
+        const double ld = t < n ? S.ldiag[t] : 1.0;
+        const double *Lj = Lt + (t < n ? t : 0) * kLtStride;
+        double x;
+        if (n < kMaxN) {
+            x = t < n ? Lj[0] : 0.0;             // y_t
+        } else {
+            // 64 rows leave no lane for the right-hand side: L y = b apart
+            x = S.rhs[t];
+            for (int i = 0; i < n; ++i) {
+                const double yi = lane_value(x, i) / lane_value(ld, i);
+                const double l = Lt[i * kLtStride + t];
+                if (t == i) x = yi;
+                else if (t > i) x -= l * yi;
+            }
+        }
+        // lane j keeps x_j; L_ij of the next row is loaded ahead of its use
+        double l = Lj[n - 1];
+        for (int i = n - 1; i >= 0; --i) {
+            const double ln = Lj[i > 0 ? i - 1 : 0];
+            const double xi = lane_value(x, i) / lane_value(ld, i);
+            const double xn = x - l * xi;
+            x = t == i ? xi : t < i ? xn : x;
+            l = ln;
+        }
+        if (t < n) S.delta[t] = x;
+        const bool good = __all(t >= n || isfinite(x));
+        if (t == 0) S.ok = good && S.pd ? 1 : 0;
+    }
+    __syncthreads();
+    return S.ok != 0;
+}
+
+// The LM decision on the evaluated trial by wave 0: acceptance, then the next
+// point (S.th_e) or the end (S.finished).  S.solve: the solve is left to the
+// whole work-group (n > 8).
+__device__ __forceinline__ void lm_decide(const Params &p, WGShared &S, const double *H2)
+{
+    const int t = threadIdx.x, n = S.n;
+    const bool simple = uniform(S.phase == 0 && S.alt_pending);
+    lm_accept(p, S);
+    if (simple) {
         // the simple start is evaluated; the next evaluation is the proposal
         // start with the other members unchanged
         if (t < 4) {
@@ -1325,38 +1520,32 @@ __device__ __forceinline__ void lm_step(const Params &p, WGShared &S, double *H2
             if (v > S.hi[t]) v = S.hi[t];
             S.th_e[t] = v;
         }
-        if (t == 0) {
-            S.alt_pending = 0;
-            S.finished = 0;
-        }
-        __syncthreads();
-        return;
+        if (t == 0) S.alt_pending = 0;
+    } else if (n <= 8) {
+        const double *Hc = H2 + S.hsel * (kMaxN * kMaxN);
+        if (n == 4) lm_solve_small<4>(p.lm_max_iter, S, Hc);
+        else lm_solve_small<8>(p.lm_max_iter, S, Hc);
     }
+    if (t == 0) S.solve = !simple && n > 8 ? 1 : 0;
+    wave_lds_sync();
+}
+
+// The next point for n > 8, by the whole work-group after lm_decide.
+__device__ __forceinline__ void lm_solve_large(const Params &p, WGShared &S, const double *H2, double *Lt)
+{
+    const int t = threadIdx.x, n = __builtin_amdgcn_readfirstlane(S.n);
     const double *Hc = H2 + S.hsel * (kMaxN * kMaxN);
-    if (n <= 8) {
-        if (t == 0) {
-            if (n == 4) lm_solve_small<4>(p.lm_max_iter, S, Hc);
-            else lm_solve_small<8>(p.lm_max_iter, S, Hc);
-        }
-        __syncthreads();
-        return;
-    }
     for (;;) {
         __syncthreads();
         if (S.finished) break;
-        if (t == 0) {
-            if (S.trials >= p.lm_max_iter) S.finished = 1;
-            else S.trials++;
-        }
         if (t < 64) {
-            // the largest diagonal entry: a max over the lanes of wave 0
-            double dmax = t < n ? Hc[t * n + t] : 0.0;
-            for (int off = 32; off > 0; off >>= 1) {
-                const double o = __shfl_xor(dmax, off, 64);
-                dmax = o > dmax ? o : dmax;
+            if (t == 0) {
+                if (S.trials >= p.lm_max_iter) S.finished = 1;
+                else S.trials++;
             }
+            const double d = t < n ? Hc[t * n + t] : 0.0;
+            const double dmax = wave_max0(d);
             if (t < n) {
-                const double d = Hc[t * n + t];
                 S.dd[t] = d < 1e-12 * dmax ? 1e-12 * dmax : d;
                 const double th = S.th_c[t], g = S.g_c[t];
                 S.frozen[t] = ((th <= S.lo[t] && g <= 0.0) || (th >= S.hi[t] && g >= 0.0)) ? 1 : 0;
@@ -1366,31 +1555,22 @@ __device__ __forceinline__ void lm_step(const Params &p, WGShared &S, double *H2
         __syncthreads();
         if (S.finished) break;
         const double mu = S.mu;
-        for (int i = t >> 4; i < n; i += 16) {
-            for (int k = t & 15; k < n; k += 16) {
-                double v;
-                if (S.frozen[i] || S.frozen[k]) v = (i == k) ? 1.0 : 0.0;
-                else v = Hc[i * n + k] + (i == k ? mu * S.dd[i] : 0.0);
-                A[i * n + k] = v;
-            }
-        }
-        if (t < n) S.rhs_copy[t] = S.rhs[t];
-        __syncthreads();
-        const bool ok = chol_solve(S, A, n, S.rhs_copy, S.delta);
+        const bool ok = chol_solve(S, Hc, n, mu, Lt);
         if (ok) {
-            if (t < n) {
-                double v = S.th_c[t] + S.delta[t];
-                if (!(v >= S.lo[t])) v = S.lo[t];
-                if (v > S.hi[t]) v = S.hi[t];
-                S.th_e[t] = v;
-            }
-            if (t == 0) {
+            if (t < 64) {
+                const double x = t < n ? S.delta[t] : 0.0;
+                const double u = t < n ? S.rhs[t] + mu * S.dd[t] * x : 0.0;
+                if (t < n) {
+                    double v = S.th_c[t] + x;
+                    if (!(v >= S.lo[t])) v = S.lo[t];
+                    if (v > S.hi[t]) v = S.hi[t];
+                    S.th_e[t] = v;
+                }
                 double pred = 0.0;
-                for (int i = 0; i < n; ++i)
-                    pred += S.delta[i] * (S.rhs[i] + mu * S.dd[i] * S.delta[i]);
-                S.pred = pred;
+                for (int i = 0; i < n; ++i) pred += lane_value(x, i) * lane_value(u, i);
+                if (t == 0) S.pred = pred;
+                wave_lds_sync();
             }
-            __syncthreads();
             break;
         }
         if (t == 0) {       // not positive definite: treated as a rejected trial
@@ -1399,7 +1579,6 @@ __device__ __forceinline__ void lm_step(const Params &p, WGShared &S, double *H2
             if (S.mu > 1e8) { S.converged = 1; S.finished = 1; }
         }
     }
-    __syncthreads();
 }
 
 // Commit and the residual-update plan, work-group 0.  The loop gain (Sect. 3)
@@ -1511,7 +1690,7 @@ __device__ __forceinline__ void commit(const Params &p, WGShared &S)
 
 // Evaluate this work-group's tiles of the trial prepared in S; its partial row
 // is left in LDS (the returned pointer), complete for every thread.
-__device__ __forceinline__ double *evaluate_row(const Params &p, WGShared &S, float *tile, double *red,
+__device__ __forceinline__ double *evaluate_row(const Params &p, WGShared &S, float *tile,
                                                 int64_t tile0, int64_t stride)
 {
     double *row = reinterpret_cast<double *>(reinterpret_cast<unsigned char *>(tile) + kRowOffset);
@@ -1521,7 +1700,7 @@ __device__ __forceinline__ double *evaluate_row(const Params &p, WGShared &S, fl
     else if (S.m <= 7) evaluate_tiles_mfma<2>(p, S, tile, tile0, stride, row);
     else if (S.m <= 11) evaluate_tiles_mfma<3>(p, S, tile, tile0, stride, row);
     else if (S.m <= 15) evaluate_tiles_mfma<4>(p, S, tile, tile0, stride, row);
-    else evaluate_tiles(p, S, tile, red, tile0, stride, row);
+    else evaluate_tiles(p, S, tile, tile0, stride, row);
     return row;
 }
 
@@ -1595,42 +1774,72 @@ __device__ __forceinline__ void arrive_released(FitGlobal *G, int wg, int gs)
                                __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// The evaluated rows 0 .. geff-1 (row 0 the leader's own, in LDS) summed into
-// He, S.ge, S.Fe, S.chi2e, S.npx_e in the association of the two-level sums:
-// rows in order within a group, then the groups in order.  `scratch` holds the
-// group sums ((n_out + 3) x groups doubles, LDS).
-__device__ __forceinline__ void reduce_flat(const Params &p, WGShared &S, int geff, int gs,
-                                            const double *row, double *He, double *scratch)
+// The evaluated rows 0 .. geff-1 (row 0 the leader's own, in LDS) of NV values
+// summed per group of gs work-groups, in row order, into `scratch` (NV x groups
+// doubles, LDS); sixteen loads in flight per thread.
+template <int NV>
+__device__ __forceinline__ void sum_groups(const Params &p, int geff, int gs, const double *row,
+                                           double *scratch)
 {
-    const int n = S.n;
-    const int nv = (n + 1) * (n + 2) / 2 + 3;
     const int ng = (geff + gs - 1) / gs;
-    for (int e = threadIdx.x; e < nv * ng; e += kT) {
-        const int o = e % nv, g = e / nv;
+    for (int e = threadIdx.x; e < NV * ng; e += kT) {
+        const int g = e / NV, o = e - g * NV;
         const int r0 = g * gs, r1 = r0 + gs < geff ? r0 + gs : geff;
         double v = 0.0;
         for (int w = r0; w < r1; w += 16) {
+            // rows past the group's last are read as the last and not added
+            const double *src = p.partials + o;
             double a[16];
 #pragma unroll
             for (int u = 0; u < 16; ++u) {
-                a[u] = 0.0;
-                if (w + u > 0 && w + u < r1)
-                    a[u] = ld_shared(p.partials + (int64_t)(w + u) * kPartStride + o);
+                const int r = w + u < r1 ? w + u : r1 - 1;
+                a[u] = ld_shared(src + (int64_t)r * kPartStride);
             }
-            if (w == 0) a[0] = row[o];
+            a[0] = w == 0 ? row[o] : a[0];
 #pragma unroll
-            for (int u = 0; u < 16; ++u)
-                if (w + u < r1) v += a[u];
+            for (int u = 0; u < 16; ++u) {
+                const double s = v + a[u];
+                v = w + u < r1 ? s : v;
+            }
         }
-        scratch[g * nv + o] = v;
+        scratch[e] = v;
     }
     __syncthreads();
-    for (int o = threadIdx.x; o < nv; o += kT) {
-        double v = scratch[o];
-        for (int g = 1; g < ng; ++g) v += scratch[g * nv + o];
-        put_sum(S, He, n, o, v);
+}
+
+// A flat trial's sums by wave 0, lane o's value o: the groups in order (the
+// association of the two-level sums), or the leader's own row (ng = 0).
+// (i, k) is the lane's Gram entry, from out_pair.
+template <int NV>
+__device__ __forceinline__ void final_sums(WGShared &S, const double *row, const double *scratch,
+                                           int ng, int i, int k, double *He)
+{
+    const int o = threadIdx.x;
+    if (o < NV) {
+        double v;
+        if (ng == 0) {
+            v = row[o];
+        } else {
+            v = scratch[o];
+            for (int g = 1; g < ng; g += 8) {
+                double a[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) a[u] = scratch[(g + u < ng ? g + u : 0) * NV + o];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const double s = v + a[u];
+                    v = g + u < ng ? s : v;
+                }
+            }
+        }
+        const int n = S.n;
+        if (o == NV - 3) S.Fe = v;
+        else if (o == NV - 2) S.chi2e = v;
+        else if (o == NV - 1) S.npx_e = (int64_t)v;
+        else if (k < n) { He[i * n + k] = v; He[k * n + i] = v; }
+        else if (i < n) S.ge[i] = v;
     }
-    __syncthreads();
+    wave_lds_sync();
 }
 
 // The peak and the stop test (Sect. 2 steps 1 and 4) of one fit, thread 0 of
@@ -1669,50 +1878,58 @@ __device__ __forceinline__ void fit_begin(const Params &p, WGShared &S, bool abo
     if (S.stop) st->stop = S.stop;
 }
 
-// One evaluation of the trial at S.th_e (old members at S.th_old) by the
-// leading work-group: F, chi2, the pixel count and [J r]^T [J r] reduced into
-// S.Fe, S.chi2e, S.npx_e, S.ge and the Gram buffer H2 + (1 - S.hsel) n^2.  A
-// trial larger than p.solo_tiles tiles is published (with the field, for a
-// batch team) and shared by the nwg work-groups.  Returns false when a wait
-// ran out; the context is then marked with ASP_ERR_DEVICE.
-__device__ __forceinline__ bool trial_eval(const Params &p, FitGlobal *G, WGShared &S, float *tile,
-                                           double *red, double *H2, int nwg, int field)
+// The trial at S.th_e, by wave 0 of the leader: member constants and windows,
+// and whether it is shared: a trial larger than p.solo_tiles tiles is published
+// (with the field, for a batch team).  S.geff: its work-groups, 0 for the
+// leader alone.
+__device__ __forceinline__ void next_trial(const Params &p, FitGlobal *G, WGShared &S, int nwg,
+                                           int field)
 {
-    DevState *st = p.st;
-    const int t = threadIdx.x;
-    prepare(p, S);
+    const bool first = uniform(S.fit_no == 0u);
+    prepare_windows(p, S);
     const int64_t ntiles = (S.pref[S.m] + kT - 1) / kT;
-    lap(S, kPPrepare);
-    double *He = H2 + (1 - S.hsel) * (kMaxN * kMaxN);   // the trial's buffer
-    if (ntiles <= p.solo_tiles) {
-        // small: the leading work-group alone, no publication
-        const double *row = evaluate_row(p, S, tile, red, 0, 1);
-        lap(S, kPEval);
-        reduce_own(S, row, He);
-        lap(S, kPReduce);
-        if (t == 0) {
-            S.prof[kPSoloTrials] += 1ull;
-            S.prof[kPSoloPx] += (unsigned long long)S.npx_e;
-        }
-        return true;
+    int geff = 0;
+    if (ntiles > p.solo_tiles) {
+        geff = eval_groups(ntiles, nwg, p.min_tiles);
+        // a batch's leader may have changed R since its last message
+        const bool release = uniform(S.epoch != S.epoch_have);
+        post(G, S, kCmdEval, geff, field, release);
+        if (threadIdx.x == 0) S.epoch_have = S.epoch;
     }
-    // large: every work-group takes a share
-    const int geff = eval_groups(ntiles, nwg, p.min_tiles);
-    const int ng_eval = (geff + p.group - 1) / p.group;
-    // a batch's leader may have changed R since its last message
-    publish(G, S, kCmdEval, geff, field, S.epoch != S.epoch_have);
-    if (t == 0) S.epoch_have = S.epoch;
-    const double *row = evaluate_row(p, S, tile, red, 0, geff);
+    if (threadIdx.x == 0) S.geff = geff;
+    // the message is on its way
+    if (first) prepare_old(p, S);
+    prepare_members(S);
+    lap(S, kPPrepare);
+}
+
+// The evaluation of the trial next_trial prepared and its sums: F, chi2, the
+// pixel count and [J r]^T [J r] into S.Fe, S.chi2e, S.npx_e, S.ge and the Gram
+// buffer H2 + (1 - S.hsel) n^2, complete for wave 0.  Returns false when a wait
+// ran out; the context is then marked with ASP_ERR_DEVICE.
+__device__ __forceinline__ bool trial_sums(const Params &p, FitGlobal *G, WGShared &S, float *tile,
+                                           double *H2, int nwg)
+{
+    const int t = threadIdx.x;
+    const int geff = S.geff, n = S.n;
+    const int ng = (geff + p.group - 1) / p.group;
+    double *He = H2 + (1 - S.hsel) * (kMaxN * kMaxN);   // the trial's buffer
+    double *scratch = reinterpret_cast<double *>(tile);
+    const double *row = evaluate_row(p, S, tile, 0, geff ? geff : 1);
     lap(S, kPEval);
-    bool ok;
-    if (S.n <= kFlatMaxN) {
-        ok = wait_groups(G, S, geff, p.group, p.spin_ticks);
-        lap(S, kPWait);
-    } else {
+    bool ok = true;
+    int i = 0, k = 0;
+    if (n <= kFlatMaxN) {
+        if (t < (n + 1) * (n + 2) / 2) out_pair(t, n, i, k);
+        if (geff) {
+            ok = wait_groups(G, S, geff, p.group, p.spin_ticks);
+            lap(S, kPWait);
+        }
+    } else if (geff) {
         arrive(p, G, S, row, 0, nwg, geff);
         lap(S, kPArrive);
         if (t == 0) {
-            S.abort = spin_until(&G->top.n, (unsigned)ng_eval, p.spin_ticks) ? 0 : 1;
+            S.abort = spin_until(&G->top.n, (unsigned)ng, p.spin_ticks) ? 0 : 1;
             st_shared(&G->top.n, 0u);
         }
         __syncthreads();
@@ -1720,15 +1937,28 @@ __device__ __forceinline__ bool trial_eval(const Params &p, FitGlobal *G, WGShar
         ok = S.abort == 0;
     }
     if (!ok) {
-        if (t == 0) st->stop = ASP_ERR_DEVICE;
+        if (t == 0) p.st->stop = ASP_ERR_DEVICE;
         __syncthreads();
         return false;
     }
-    if (S.n <= kFlatMaxN)
-        reduce_flat(p, S, geff, p.group, row, He, reinterpret_cast<double *>(tile));
-    else if (ng_eval > 1) reduce_partials(p, S, nwg, nwg + ng_eval, He);
-    else reduce_partials(p, S, 0, geff, He);
+    if (n == 4) {
+        if (geff) sum_groups<18>(p, geff, p.group, row, scratch);
+        if (t < 64) final_sums<18>(S, row, scratch, ng, i, k, He);
+    } else if (n == 8) {
+        if (geff) sum_groups<48>(p, geff, p.group, row, scratch);
+        if (t < 64) final_sums<48>(S, row, scratch, ng, i, k, He);
+    } else {
+        const int nv = (n + 1) * (n + 2) / 2 + 3;
+        const int w0 = ng > 1 ? nwg : 0, w1 = ng > 1 ? nwg + ng : geff;
+        for (int o = t; o < nv; o += kT)
+            put_sum(S, He, n, o, geff ? sum_column(p, w0, w1, o) : row[o]);
+        __syncthreads();
+    }
     lap(S, kPReduce);
+    if (t == 0 && geff == 0) {
+        S.prof[kPSoloTrials] += 1ull;
+        S.prof[kPSoloPx] += (unsigned long long)S.npx_e;
+    }
     return true;
 }
 
@@ -1736,63 +1966,79 @@ __device__ __forceinline__ bool trial_eval(const Params &p, FitGlobal *G, WGShar
 // leading work-group (share 0 of nwg).  Returns false when a wait ran out; the
 // context is then marked with ASP_ERR_DEVICE.
 __device__ __forceinline__ bool fit_trials(const Params &p, FitGlobal *G, WGShared &S, float *tile,
-                                           double *red, double *A, double *H2,
-                                           int nwg, int field)
+                                           double *H2, int nwg, int field)
 {
     DevState *st = p.st;
     const int t = threadIdx.x;
     mark(S);
     if (t == 0) S.tfit = S.tmark;
-    setup_fit(p, S, S.use_prop != 0);
-    lap(S, kPSetup);
     for (;;) {
-        if (!trial_eval(p, G, S, tile, red, H2, nwg, field)) return false;
-        lm_step(p, S, H2, A);
-        lap(S, kPLmStep);
-        if (t == 0) {
-            const unsigned long long npx = (unsigned long long)S.npx_e;
-            S.eval_px += npx;
-            S.gram_flops += npx * (unsigned long long)((S.n + 1) * (S.n + 2));
-            S.prof[kPTrials] += 1ull;
-            S.prof[kPEvalPx] += npx;
+        setup_fit(p, S, S.use_prop != 0 && S.pass == 0);
+        lap(S, kPSetup);
+        if (t < 64) next_trial(p, G, S, nwg, field);
+        __syncthreads();
+        for (;;) {
+            if (!trial_sums(p, G, S, tile, H2, nwg)) return false;
+            if (t < 64) {
+                if (t == 0) {
+                    const unsigned long long npx = (unsigned long long)S.npx_e;
+                    S.eval_px += npx;
+                    S.gram_flops += npx * (unsigned long long)((S.n + 1) * (S.n + 2));
+                    S.prof[kPTrials] += 1ull;
+                    S.prof[kPEvalPx] += npx;
+                }
+                lm_decide(p, S, H2);
+                if (S.n <= kFlatMaxN || !uniform(S.solve != 0)) {
+                    lap(S, kPLmStep);
+                    if (!uniform(S.finished != 0)) next_trial(p, G, S, nwg, field);
+                }
+            }
+            __syncthreads();
+            if (S.solve) {
+                lm_solve_large(p, S, H2, reinterpret_cast<double *>(tile));
+                if (t < 64) {
+                    lap(S, kPLmStep);
+                    if (!uniform(S.finished != 0)) next_trial(p, G, S, nwg, field);
+                }
+                __syncthreads();
+            }
+            if (S.finished) break;
         }
-        if (!S.finished) continue;
         if (S.use_prop && S.chose_prop && S.pass == 0 && (!S.converged || S.th_c[0] == 0.0)) {
             // LM started from the proposal and did not converge, or converged
             // to a new component of zero amplitude (which can leave the model
             // unchanged, so that the same peak and proposal come back): the
             // simple values instead
+            __syncthreads();
             if (t == 0) {
                 S.trials_total += S.trials;
                 S.used_fallback = 1;
                 S.pass = 1;
             }
             __syncthreads();
-            setup_fit(p, S, false);
             continue;
         }
-        mark(S);
-        commit(p, S);
-        lap(S, kPCommit);
-        if (t == 0) {
-            const int m = S.m;
-            st->fits_m[m] += 1ull;
-            st->trials_m[m] += (unsigned long long)(S.trials_total + S.trials);
-            st->ticks_m[m] += now_ticks() - S.tfit;
-        }
-        flush_counts(p, S);
-        return true;
+        break;
     }
+    mark(S);
+    commit(p, S);
+    lap(S, kPCommit);
+    if (t == 0) {
+        const int m = S.m;
+        st->fits_m[m] += 1ull;
+        st->trials_m[m] += (unsigned long long)(S.trials_total + S.trials);
+        st->ticks_m[m] += now_ticks() - S.tfit;
+    }
+    flush_counts(p, S);
+    return true;
 }
 
 __global__ __launch_bounds__(kT) void k_fit(Params p)
 {
     extern __shared__ __align__(16) unsigned char lds[];
     float *tile = reinterpret_cast<float *>(lds);
-    double *A = reinterpret_cast<double *>(lds);               // shares the tile buffer
     double *H2 = reinterpret_cast<double *>(lds + kTileBytes);   // two Gram buffers
     __shared__ WGShared S;
-    __shared__ double red[kT];
     FitGlobal *G = p.fg;
     DevState *st = p.st;
     const int t = threadIdx.x;
@@ -1822,7 +2068,16 @@ __global__ __launch_bounds__(kT) void k_fit(Params p)
         // the workers need no acquire fence: their L2 keeps the residual's
         // lines from trial to trial.
         for (;;) {
-            if (!wait_mail(G, S, wg, p.spin_ticks)) {
+            if (t < 64) {
+                wait_mail(G, S, wg, p.spin_ticks);
+                if (uniform(S.abort == 0 && S.cmd == kCmdEval && wg < S.geff)) {
+                    if (uniform(S.fresh != 0)) prepare_old(p, S);
+                    prepare_windows(p, S);
+                    prepare_members(S);
+                }
+            }
+            __syncthreads();
+            if (S.abort) {
                 if (t == 0) st->stop = ASP_ERR_DEVICE;
                 return;
             }
@@ -1837,8 +2092,7 @@ __global__ __launch_bounds__(kT) void k_fit(Params p)
             if (S.cmd != kCmdEval) return;
             const int geff = S.geff;
             if (wg < geff) {
-                prepare(p, S);
-                const double *row = evaluate_row(p, S, tile, red, wg, geff);
+                const double *row = evaluate_row(p, S, tile, wg, geff);
                 arrive(p, G, S, row, wg, nwg, geff);
             }
             __syncthreads();               // S is rewritten by the next message
@@ -1866,7 +2120,11 @@ __global__ __launch_bounds__(kT) void k_fit(Params p)
             S.th_old[t] = st->diag_stored[t];
         }
         __syncthreads();
-        const bool ok = !S.abort && trial_eval(p, G, S, tile, red, H2, nwg, 0);
+        bool ok = !S.abort;
+        if (t < 64 && ok) next_trial(p, G, S, nwg, 0);
+        __syncthreads();
+        ok = ok && trial_sums(p, G, S, tile, H2, nwg);
+        __syncthreads();
         const int n = S.n;
         double *o = st->diag_out;
         if (ok) {
@@ -1894,7 +2152,7 @@ __global__ __launch_bounds__(kT) void k_fit(Params p)
     }
     __syncthreads();
     if (!S.stop) {
-        const bool committed = fit_trials(p, G, S, tile, red, A, H2, nwg, 0);
+        const bool committed = fit_trials(p, G, S, tile, H2, nwg, 0);
         // with fuse_update every work-group takes its tiles of the update
         // (Sect. 2 step 3) after this publication; the end of the kernel is
         // the barrier before the next iteration reads R
@@ -1904,7 +2162,7 @@ __global__ __launch_bounds__(kT) void k_fit(Params p)
     }
     __syncthreads();
     const bool upd = S.upd != 0;
-    publish(G, S, upd ? kCmdUpdate : kCmdExit, 0, 0, upd);
+    publish(G, S, upd ? kCmdUpdate : kCmdExit, 0, upd);
     if (upd) update_tiles(p, 0, nwg, tile);
 }
 
@@ -1952,10 +2210,8 @@ __global__ __launch_bounds__(kT) void k_batch(BatchArgs b)
 {
     extern __shared__ __align__(16) unsigned char lds[];
     float *tile = reinterpret_cast<float *>(lds);
-    double *A = reinterpret_cast<double *>(lds);
     double *H2 = reinterpret_cast<double *>(lds + kTileBytes);   // two Gram buffers
     __shared__ WGShared S;
-    __shared__ double red[kT];
     __shared__ Params P;
     __shared__ int32_t cur_field;
     const int t = threadIdx.x;
@@ -1981,7 +2237,9 @@ __global__ __launch_bounds__(kT) void k_batch(BatchArgs b)
 
     if (rank != 0) {
         for (;;) {
-            if (!wait_mail(G, S, rank, b.spin_ticks, true)) return;  // the leader marks its field
+            if (t < 64) wait_mail(G, S, rank, b.spin_ticks, true);
+            __syncthreads();
+            if (S.abort) return;                     // the leader marks its field
             const int cmd = S.cmd;
             if (cmd == kCmdExit || S.fld < 0 || S.fld >= b.n_fields) return;
             if (S.epoch != S.epoch_have) {
@@ -2008,8 +2266,13 @@ __global__ __launch_bounds__(kT) void k_batch(BatchArgs b)
             } else if (cmd == kCmdEval) {
                 const int geff = S.geff;
                 if (rank < geff) {
-                    prepare(P, S);
-                    const double *row = evaluate_row(P, S, tile, red, rank, geff);
+                    if (t < 64) {
+                        if (uniform(S.fresh != 0)) prepare_old(P, S);
+                        prepare_windows(P, S);
+                        prepare_members(S);
+                    }
+                    __syncthreads();
+                    const double *row = evaluate_row(P, S, tile, rank, geff);
                     arrive(P, G, S, row, rank, T, geff);
                 }
             }
@@ -2050,7 +2313,7 @@ __global__ __launch_bounds__(kT) void k_batch(BatchArgs b)
             if (T == 1 || npx <= b.solo_peak_px) {
                 peak_scan(P.R, npx, 0u, 1u, P.st->peak_keys);
             } else {
-                publish(G, S, kCmdPeak, 0, cur_field, true);
+                publish(G, S, kCmdPeak, cur_field, true);
                 if (t == 0) S.epoch_have = S.epoch;
                 peak_scan(P.R, npx, 0u, (uint32_t)T, P.st->peak_keys);
                 if (!team_wait(G, S, T, b.spin_ticks)) { ok = false; break; }
@@ -2061,7 +2324,7 @@ __global__ __launch_bounds__(kT) void k_batch(BatchArgs b)
             if (t == 0) fit_begin(P, S, false);
             __syncthreads();
             if (S.stop) break;
-            if (!fit_trials(P, G, S, tile, red, A, H2, T, cur_field)) { ok = false; break; }
+            if (!fit_trials(P, G, S, tile, H2, T, cur_field)) { ok = false; break; }
             // the residual update (Sect. 2 step 3)
             if (t == 0) {
                 const int32_t *bb = P.st->bb;
@@ -2072,17 +2335,18 @@ __global__ __launch_bounds__(kT) void k_batch(BatchArgs b)
                 update_tiles<1>(P, 0, 1, tile);
             } else {
                 if (t == 0) S.epoch += 1u;     // the plan
-                publish(G, S, kCmdUpdate, 0, cur_field, true);
+                publish(G, S, kCmdUpdate, cur_field, true);
                 update_tiles<1>(P, 0, T, tile);
                 if (!team_wait(G, S, T, b.spin_ticks)) { ok = false; break; }
             }
+            wave_stores_done();                // for the release of a later message
             __syncthreads();
             if (t == 0) S.epoch += 1u;         // R
         }
     }
     if (!ok && t == 0 && cur_field >= 0) P.st->stop = ASP_ERR_DEVICE;
     __syncthreads();
-    if (T > 1) publish(G, S, kCmdExit, 0, 0, true);
+    if (T > 1) publish(G, S, kCmdExit, 0, true);
 }
 
 __global__ void k_batch_reset(unsigned int *queue) { *queue = 0u; }
