@@ -91,6 +91,93 @@ __device__ inline void peak_scan(const float *__restrict__ R, int64_t n, uint32_
 }
 
 // ===========================================================================
+// Incremental peak search: the listed tiles of R, whose windows an update has
+// touched, are scanned again, and the largest of all tile keys is the peak's.
+// ===========================================================================
+
+// Share `rank` of `size` of the listed tiles.  Lane = column of the tile, wave w
+// = rows w, w + 4, ...: every load of a wave is one 256-byte row segment.
+__device__ inline void peak_tiles_scan(const Params &p, unsigned int rank, unsigned int size)
+{
+    const PeakTiles K = p.st->pk;
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+    const int tx = K.tiles_x;
+    const unsigned int n = __hip_atomic_load(K.count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const int64_t H = p.H, W = p.W;
+    __shared__ unsigned long long wk[4];
+    constexpr int kRows = kPkTile / 4;
+    for (unsigned int i = rank; i < n; i += size) {
+        const int tile = K.list[i];
+        const int64_t r0 = (int64_t)(tile / tx) * kPkTile;
+        const int64_t c = (int64_t)(tile % tx) * kPkTile + lane;
+        unsigned long long best = 0;
+        if (c < W) {
+            // rows in increasing order, strict maximum: the lowest index of a tie
+            float v[kRows];
+#pragma unroll
+            for (int k = 0; k < kRows; ++k) {
+                const int64_t r = r0 + w + 4 * k;
+                v[k] = r < H ? p.R[r * W + c] : 0.0f;
+            }
+            float bv = -1.0f;
+            int64_t bi = 0;
+#pragma unroll
+            for (int k = 0; k < kRows; ++k) {
+                const int64_t r = r0 + w + 4 * k;
+                const float a = fabsf(v[k]);
+                if (r < H && a > bv) { bv = a; bi = r * W + c; }
+            }
+            if (bv >= 0.0f)
+                best = ((unsigned long long)__float_as_uint(bv) << 32) |
+                       (unsigned long long)(0xFFFFFFFFu - (uint32_t)bi);
+        }
+        best = wave_max_u64(best);
+        __syncthreads();                   // wk of the previous tile is read
+        if (lane == 0) wk[w] = best;
+        __syncthreads();
+        if (t == 0) {
+            unsigned long long m = wk[0];
+            for (int k = 1; k < 4; ++k) m = wk[k] > m ? wk[k] : m;
+            K.keys[tile] = m;
+            K.dirty[tile] = 0;
+            atomicAdd(&p.st->pk_tiles_done, 1ull);
+        }
+    }
+}
+
+// The maximum of the tile keys into the peak key (slot 0; the slots are
+// cleared by whoever consumes the key), and the list is emptied.  One
+// work-group of up to sixteen waves.
+__device__ inline void peak_tiles_reduce(const Params &p)
+{
+    const PeakTiles K = p.st->pk;
+    const int t = threadIdx.x, nt = blockDim.x;
+    if (t == 0) __hip_atomic_store(K.count, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const int ntiles = K.tiles_x * K.tiles_y;
+    unsigned long long best = 0;
+    int i = t;
+    for (; i + 7 * nt < ntiles; i += 8 * nt) {
+        unsigned long long k[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) k[u] = K.keys[i + u * nt];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) best = k[u] > best ? k[u] : best;
+    }
+    for (; i < ntiles; i += nt) best = K.keys[i] > best ? K.keys[i] : best;
+    best = wave_max_u64(best);
+    __shared__ unsigned long long wk[16];
+    if ((t & 63) == 0) wk[t >> 6] = best;
+    __syncthreads();
+    if (t == 0) {
+        unsigned long long m = wk[0];
+        for (int k = 1; k < nt >> 6; ++k) m = wk[k] > m ? wk[k] : m;
+        atomicMax(&p.st->peak_keys[0], m);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // before this work-group collects it
+    }
+    __syncthreads();
+}
+
+// ===========================================================================
 // Residual update: R += sum over the plan's rects of sign * G on the rect,
 // each pixel read and written once (Sect. 2 step 3 with the Gaussian beam).
 // Blocks stride over tiles of the plan's bounding box, 256 columns (origin a

@@ -1774,6 +1774,25 @@ __device__ __forceinline__ void arrive_released(FitGlobal *G, int wg, int gs)
                                __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// The leader's wait for the arrivals of work-groups 1 .. T-1 after a command on
+// plain data, and the acquire of what they wrote; false when it ran out.
+__device__ __forceinline__ bool team_wait(FitGlobal *G, WGShared &S, int T, int gs,
+                                          unsigned long long limit)
+{
+    const bool ok = wait_groups(G, S, T, gs, limit);
+    if (threadIdx.x == 0) acquire_fence();
+    __syncthreads();
+    return ok;
+}
+
+// Work-group `wg`'s share of the peak search (Sect. 2 step 1): of the whole
+// residual, or of the listed tiles.
+__device__ __forceinline__ void peak_share(const Params &p, int wg, int nwg)
+{
+    if (p.st->pk.tiles_x > 0) peak_tiles_scan(p, (unsigned)wg, (unsigned)nwg);
+    else peak_scan(p.R, p.H * p.W, (uint32_t)wg, (uint32_t)nwg, p.st->peak_keys);
+}
+
 // The evaluated rows 0 .. geff-1 (row 0 the leader's own, in LDS) of NV values
 // summed per group of gs work-groups, in row order, into `scratch` (NV x groups
 // doubles, LDS); sixteen loads in flight per thread.
@@ -2063,10 +2082,10 @@ __global__ __launch_bounds__(kT) void k_fit(Params p)
 
     if (wg != 0) {
         // Workers: evaluate the shared trials work-group 0 publishes.
-        // The residual does not change before the update at the end of this
-        // kernel and everything else that crosses is read with atomic loads, so
-        // the workers need no acquire fence: their L2 keeps the residual's
-        // lines from trial to trial.
+        // The residual does not change before the update at the end of an
+        // iteration and everything else that crosses is read with atomic loads,
+        // so the workers need no acquire fence for a trial: their L2 keeps the
+        // residual's lines from trial to trial.
         for (;;) {
             if (t < 64) {
                 wait_mail(G, S, wg, p.spin_ticks);
@@ -2081,13 +2100,18 @@ __global__ __launch_bounds__(kT) void k_fit(Params p)
                 if (t == 0) st->stop = ASP_ERR_DEVICE;
                 return;
             }
-            if (S.cmd == kCmdUpdate) {
-                // the committed plan was written by work-group 0 with plain
-                // stores: acquire before reading it
+            if (S.cmd == kCmdUpdate || S.cmd == kCmdPeak) {
+                // the plan was written by work-group 0, and the residual by
+                // every work-group, with plain stores: acquire before reading
+                const bool peak = S.cmd == kCmdPeak, last = S.fld != 0;
                 if (t == 0) acquire_fence();
                 __syncthreads();
-                update_tiles(p, wg, nwg, tile);
-                return;
+                if (peak) peak_share(p, wg, nwg);
+                else update_tiles(p, wg, nwg, tile);
+                if (last) return;
+                arrive_released(G, wg, p.group);
+                __syncthreads();
+                continue;
             }
             if (S.cmd != kCmdEval) return;
             const int geff = S.geff;
@@ -2145,25 +2169,39 @@ __global__ __launch_bounds__(kT) void k_fit(Params p)
         publish(G, S, kCmdExit);
         return;
     }
-    collect_peak_key(st, true, &S.key);
-    if (t == 0) {
-        fit_begin(p, S, S.abort != 0);
-        S.upd = 0;
+    for (int it = 1;; ++it) {
+        if (p.iters > 0 && S.abort == 0) {
+            publish(G, S, kCmdPeak, 0, true);
+            peak_share(p, 0, nwg);
+            wave_stores_done();
+            team_wait(G, S, nwg, p.group, p.spin_ticks);
+            if (st->pk.tiles_x > 0) peak_tiles_reduce(p);
+        }
+        collect_peak_key(st, true, &S.key);
+        if (t == 0) {
+            fit_begin(p, S, S.abort != 0);
+            S.upd = 0;
+        }
+        __syncthreads();
+        if (!S.stop) {
+            const bool committed = fit_trials(p, G, S, tile, H2, nwg, 0);
+            // with fuse_update every work-group takes its tiles of the update
+            // (Sect. 2 step 3) after this publication; the end of the kernel,
+            // or the wait for every work-group, is the barrier before the next
+            // iteration reads R
+            if (t == 0) S.upd = committed && p.fuse_update ? 1 : 0;
+        } else {
+            flush_counts(p, S);
+        }
+        __syncthreads();
+        const bool upd = S.upd != 0, last = !upd || it >= p.iters;
+        publish(G, S, upd ? kCmdUpdate : kCmdExit, last ? 1 : 0, upd);
+        if (upd) update_tiles(p, 0, nwg, tile);
+        if (last) return;
+        wave_stores_done();
+        team_wait(G, S, nwg, p.group, p.spin_ticks);
+        mark(S);
     }
-    __syncthreads();
-    if (!S.stop) {
-        const bool committed = fit_trials(p, G, S, tile, H2, nwg, 0);
-        // with fuse_update every work-group takes its tiles of the update
-        // (Sect. 2 step 3) after this publication; the end of the kernel is
-        // the barrier before the next iteration reads R
-        if (t == 0) S.upd = committed && p.fuse_update ? 1 : 0;
-    } else {
-        flush_counts(p, S);
-    }
-    __syncthreads();
-    const bool upd = S.upd != 0;
-    publish(G, S, upd ? kCmdUpdate : kCmdExit, 0, upd);
-    if (upd) update_tiles(p, 0, nwg, tile);
 }
 
 // ===========================================================================
@@ -2194,16 +2232,6 @@ __device__ __forceinline__ void load_field(const BatchArgs &b, int f, FitGlobal 
         P.group = kGroup;
     }
     __syncthreads();
-}
-
-// The leader's wait for the team's arrivals after a command on plain data, and
-// the acquire of what they wrote; false when it ran out.
-__device__ __forceinline__ bool team_wait(FitGlobal *G, WGShared &S, int T, unsigned long long limit)
-{
-    const bool ok = wait_groups(G, S, T, kGroup, limit);
-    if (threadIdx.x == 0) acquire_fence();
-    __syncthreads();
-    return ok;
 }
 
 __global__ __launch_bounds__(kT) void k_batch(BatchArgs b)
@@ -2316,7 +2344,7 @@ __global__ __launch_bounds__(kT) void k_batch(BatchArgs b)
                 publish(G, S, kCmdPeak, cur_field, true);
                 if (t == 0) S.epoch_have = S.epoch;
                 peak_scan(P.R, npx, 0u, (uint32_t)T, P.st->peak_keys);
-                if (!team_wait(G, S, T, b.spin_ticks)) { ok = false; break; }
+                if (!team_wait(G, S, T, kGroup, b.spin_ticks)) { ok = false; break; }
             }
             __syncthreads();
             // the stop test and the fit (Sect. 2 step 4; Sect. 3)
@@ -2337,7 +2365,7 @@ __global__ __launch_bounds__(kT) void k_batch(BatchArgs b)
                 if (t == 0) S.epoch += 1u;     // the plan
                 publish(G, S, kCmdUpdate, cur_field, true);
                 update_tiles<1>(P, 0, T, tile);
-                if (!team_wait(G, S, T, b.spin_ticks)) { ok = false; break; }
+                if (!team_wait(G, S, T, kGroup, b.spin_ticks)) { ok = false; break; }
             }
             wave_stores_done();                // for the release of a later message
             __syncthreads();

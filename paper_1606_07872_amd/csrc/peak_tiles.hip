@@ -8,6 +8,7 @@
 // key.  The packed key (|v| bits << 32) | (0xFFFFFFFF - idx) is the one of the
 // full scan, so the result is the same pixel bit for bit.
 #include "asp_device.h"
+#include "cycle.h"
 
 namespace asp {
 namespace {
@@ -16,83 +17,17 @@ constexpr int kT = 256;
 constexpr int kReduceT = 1024;
 constexpr int kTileGrid = 1024;
 
-__device__ inline unsigned long long wave_max(unsigned long long v)
-{
-    for (int off = 32; off > 0; off >>= 1) {
-        const unsigned long long o = __shfl_xor(v, off, 64);
-        v = o > v ? o : v;
-    }
-    return v;
-}
-
-// Lane = column of the tile, wave w = rows w, w + 4, ...: every load of a wave
-// is one 256-byte row segment.
 __global__ __launch_bounds__(kT) void k_peak_tiles(Params p)
 {
     if (p.st->stop) return;
-    const PeakTiles K = p.st->pk;
-    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-    const int tx = K.tiles_x;
-    const unsigned int n = K.count[0];
-    const int64_t H = p.H, W = p.W;
-    __shared__ unsigned long long wk[kT / 64];
-    for (unsigned int i = blockIdx.x; i < n; i += gridDim.x) {
-        const int tile = K.list[i];
-        const int64_t r0 = (int64_t)(tile / tx) * kPkTile;
-        const int64_t c = (int64_t)(tile % tx) * kPkTile + lane;
-        unsigned long long best = 0;
-        if (c < W) {
-            // rows in increasing order, strict maximum: the lowest index of a tie
-            float bv = -1.0f;
-            int64_t bi = 0;
-            for (int rr = w; rr < kPkTile; rr += kT / 64) {
-                const int64_t r = r0 + rr;
-                if (r >= H) break;
-                const float a = fabsf(p.R[r * W + c]);
-                if (a > bv) { bv = a; bi = r * W + c; }
-            }
-            if (bv >= 0.0f)
-                best = ((unsigned long long)__float_as_uint(bv) << 32) |
-                       (unsigned long long)(0xFFFFFFFFu - (uint32_t)bi);
-        }
-        best = wave_max(best);
-        __syncthreads();                   // wk of the previous tile is read
-        if (lane == 0) wk[w] = best;
-        __syncthreads();
-        if (t == 0) {
-            unsigned long long m = wk[0];
-            for (int k = 1; k < kT / 64; ++k) m = wk[k] > m ? wk[k] : m;
-            K.keys[tile] = m;
-            K.dirty[tile] = 0;
-            atomicAdd(&p.st->pk_tiles_done, 1ull);
-        }
-    }
+    peak_tiles_scan(p, blockIdx.x, gridDim.x);
 }
 
-// The maximum of the tile keys into the peak key (slot 0; the slots are
-// cleared by whoever consumes the key).  The tile pass has finished: its list
-// is emptied here.
+// The tile pass has finished.
 __global__ __launch_bounds__(kReduceT) void k_peak_reduce(Params p)
 {
     if (p.st->stop) return;
-    const PeakTiles K = p.st->pk;
-    const int t = threadIdx.x;
-    if (t == 0) K.count[0] = 0;
-    const int ntiles = K.tiles_x * K.tiles_y;
-    unsigned long long best = 0;
-    for (int i = t; i < ntiles; i += kReduceT) {
-        const unsigned long long k = K.keys[i];
-        best = k > best ? k : best;
-    }
-    best = wave_max(best);
-    __shared__ unsigned long long wk[kReduceT / 64];
-    if ((t & 63) == 0) wk[t >> 6] = best;
-    __syncthreads();
-    if (t == 0) {
-        unsigned long long m = wk[0];
-        for (int k = 1; k < kReduceT / 64; ++k) m = wk[k] > m ? wk[k] : m;
-        atomicMax(&p.st->peak_keys[0], m);
-    }
+    peak_tiles_reduce(p);
 }
 
 __global__ __launch_bounds__(kT) void k_peak_mark_all(Params p)

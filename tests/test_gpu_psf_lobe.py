@@ -5,7 +5,6 @@ import numpy as np
 import pytest
 
 import oracle
-from parity import PARAM_RTOL
 
 pytestmark = pytest.mark.gpu
 
@@ -38,6 +37,6 @@ def test_lobe(name):
     ctx = asp.Context(dirty, psf, 0.1, 0.0, max_iter=1)
     ab, wb = ctx.psf_gauss()
     ao, wo = oracle.psf_fit(psf)[:2]
-    assert abs(ab - ao) <= PARAM_RTOL * abs(ao), (ab, ao)
-    assert abs(wb - wo) <= PARAM_RTOL * abs(wo), (wb, wo)
+    assert abs(ab - ao) <= 1e-6 * abs(ao), (ab, ao)
+    assert abs(wb - wo) <= 1e-6 * abs(wo), (wb, wo)
     ctx.close()
