@@ -200,22 +200,32 @@ asp_status setup_smoothing(asp_ctx *c)
     }
     if ((double)N * (double)n >= 4294967295.0)
         return fail(c, ASP_ERR_INVALID_ARG, "image too large for the smoothing method's keys");
-    // norm factors 1 / sqrt(sum of k^2 over the clipped 1-D window), FP64
+    // norm factors 1 / sqrt(sum of k^2 over the clipped 1-D window), FP64; away
+    // from the edges the window is whole and the factor the same (the sums with
+    // an exponential per term and pixel took 2.8 ms at 1024 x 1024, five scales)
     std::vector<float> w((size_t)n * (W + H));
+    std::vector<double> k2;
     for (int j = 0; j < n; ++j) {
-        const int h = S.h[j];
+        const int64_t h = S.h[j];
         const double sig = S.sig[j];
-        auto f = [&](int64_t pos, int64_t len) {
+        k2.resize((size_t)(2 * h + 1));
+        for (int64_t d = -h; d <= h; ++d) {
+            const double k = exp(-((double)d * d) / (2.0 * sig * sig));
+            k2[(size_t)(d + h)] = k * k;
+        }
+        auto f = [&](int64_t lo, int64_t hi) {
             double acc = 0.0;
-            for (int d = -h; d <= h; ++d) {
-                if (pos + d < 0 || pos + d >= len) continue;
-                const double k = exp(-((double)d * d) / (2.0 * sig * sig));
-                acc += k * k;
-            }
+            for (int64_t d = lo; d <= hi; ++d) acc += k2[(size_t)(d + h)];
             return (float)(1.0 / sqrt(acc));
         };
-        for (int64_t x = 0; x < W; ++x) w[(size_t)j * W + x] = f(x, W);
-        for (int64_t y = 0; y < H; ++y) w[(size_t)n * W + (size_t)j * H + y] = f(y, H);
+        const float whole = f(-h, h);
+        auto fill = [&](float *v, int64_t len) {
+            for (int64_t x = 0; x < len; ++x)
+                v[x] = x >= h && x + h < len ? whole
+                                             : f(x < h ? -x : -h, x + h < len ? h : len - 1 - x);
+        };
+        fill(&w[(size_t)j * W], W);
+        fill(&w[(size_t)n * W + (size_t)j * H], H);
     }
     S.n = n;
     S.norm = c->opt.smooth_norm;
