@@ -413,11 +413,56 @@ constexpr int kYR = 16;    // output rows per tile of the column pass (four per 
 constexpr int kYC = 64;    // output columns per tile (one per lane)
 constexpr int kYK = 32;    // row taps per chunk
 
+// One chunk of kc row taps for a wave's RW output rows (wq RW, ... of the tile)
+// in its lane's column, T rows in increasing order.  Output row k meets T row
+// l0 + i with tap k + kc - 1 - i: the taps slide through registers, one new one
+// per T row, and the zeros around a chunk's taps (kYPad on each side) stand
+// where a row has none, so that the loop has no branch.
+constexpr int kYPad = 3;
+template <bool Final, int RW>
+__device__ __forceinline__ void column_chunk(const double (*Ts)[kYR + kYK - 1][kYC],
+                                             const double (*ts)[kYK + 2 * kYPad], int kc, int wq, int lane,
+                                             double (*acc)[Final ? 1 : 4])
+{
+    static_assert(RW - 1 <= kYPad, "zeros around the taps");
+    constexpr int NP = Final ? 1 : 3, NJ = Final ? 1 : 4;
+    const int l0 = RW * wq;
+    double w[NP][RW];
+#pragma unroll
+    for (int q = 0; q < NP; ++q)
+#pragma unroll
+        for (int k = 0; k < RW; ++k) w[q][k] = 0.0;
+#pragma unroll 4
+    for (int i = 0; i < kc + RW - 1; ++i) {
+        double t[NP];
+#pragma unroll
+        for (int q = 0; q < NP; ++q) {
+#pragma unroll
+            for (int k = RW - 1; k > 0; --k) w[q][k] = w[q][k - 1];
+            w[q][0] = ts[q][kYPad + kc - 1 - i];
+            t[q] = Ts[q][l0 + i][lane];
+        }
+#pragma unroll
+        for (int k = 0; k < RW; ++k) {
+            const double w0 = w[0][k];
+            acc[k][0] += w0 * t[0];
+            if (!Final) {
+                acc[k][1 % NJ] += w0 * t[1 % NP];
+                acc[k][2 % NJ] += w[1 % NP][k] * t[0];
+                acc[k][3 % NJ] += w[2 % NP][k] * t[0] + w0 * t[2 % NP];
+            }
+        }
+    }
+}
+
 // Column pass over tiles of 4 RW rows x kYC columns (work-group b takes tiles
 // b, b + nblk, ...), RW = 4 rows per wave, or 1 where tiles of 16 rows would
 // leave work-groups idle (small images).  Per chunk of row taps the
-// work-group stages the rows of T it reaches in LDS, then wave w accumulates
-// output rows RW w .. RW w + RW - 1 of its lane's column.  Then per pixel the
+// work-group stages the rows of T it reaches in LDS, while the next chunk's are
+// on their way, then wave w accumulates output rows RW w .. RW w + RW - 1 of its
+// lane's column.  Bound by the FP64 FMAs of one wave per SIMD: at 512 x 512 25 us
+// an evaluation, 36 with a test per row and tap and a plane loaded at a time.
+// Then per pixel the
 // sums of k_a4_gram, reduced in the same fixed order into partial row b; or,
 // for the update, R -= gain F B(*)g.
 template <bool Final>
@@ -426,7 +471,7 @@ __global__ __launch_bounds__(kT) void k_a4_ypass(A4Args a)
     if (Final ? !finished(a) : !live(a)) return;
     constexpr int NJ = Final ? 1 : 4, NP = Final ? 1 : 3;
     __shared__ double Ts[NP][kYR + kYK - 1][kYC];
-    __shared__ double ts[NP][kYK];
+    __shared__ double ts[NP][kYK + 2 * kYPad];
     const int64_t nc = a.tapi[1], nr = a.tapi[3];
     const int64_t H = a.H, W = a.W;
     const bool empty = nc == 0 || nr == 0;
@@ -449,53 +494,43 @@ __global__ __launch_bounds__(kT) void k_a4_ypass(A4Args a)
         for (int k = 0; k < 4; ++k)
 #pragma unroll
             for (int q = 0; q < NJ; ++q) acc[k][q] = 0.0;
-        for (int64_t i0 = 0; !empty && i0 < nr; i0 += kYK) {
+        // output row ra + lr with tap i0 + di reads T row ybase + ly,
+        // ly = lr + kc - 1 - di; wave wq stages rows wq, wq + 4, ..., all its
+        // loads of a chunk in flight together
+        constexpr int kU = (kYR + kYK - 1 + 3) / 4;
+        double v[NP][kU];
+        auto fetch = [&](int64_t i0) __attribute__((always_inline)) {
             const int kc = (int)(nr - i0 < kYK ? nr - i0 : kYK);
-            // output row ra + lr with tap i0 + di reads T row ybase + ly,
-            // ly = lr + kc - 1 - di
             const int64_t ybase = ra + nr - 1 - i0 - (kc - 1);
-            const int nrows = TR + kc - 1;
-            __syncthreads();
-            // wave wq stages rows wq, wq + 4, ...: twelve loads in flight per plane
-            constexpr int kU = (kYR + kYK - 1 + 3) / 4;
 #pragma unroll
-            for (int p = 0; p < NP; ++p) {
-                double v[kU];
+            for (int p = 0; p < NP; ++p)
 #pragma unroll
                 for (int u = 0; u < kU; ++u) {
                     const int ly = wq + 4 * u;
                     const int64_t y = ybase + ly;
-                    v[u] = ly < nrows && y < Ny && c < W ? a.grid[p * plane + y * W + c] : 0.0;
+                    v[p][u] = ly < TR + kc - 1 && y < Ny && c < W ? a.grid[p * plane + y * W + c] : 0.0;
                 }
+        };
+        if (!empty) fetch(0);
+        for (int64_t i0 = 0; !empty && i0 < nr; i0 += kYK) {
+            const int kc = (int)(nr - i0 < kYK ? nr - i0 : kYK);
+            __syncthreads();
+#pragma unroll
+            for (int p = 0; p < NP; ++p)
 #pragma unroll
                 for (int u = 0; u < kU; ++u) {
                     const int ly = wq + 4 * u;
-                    if (ly < nrows) Ts[p][ly][lane] = v[u];
+                    if (ly < TR + kc - 1) Ts[p][ly][lane] = v[p][u];
                 }
-            }
-            if (threadIdx.x < kc) {
+            if (threadIdx.x < kYK + 2 * kYPad) {
+                const int di = (int)threadIdx.x - kYPad;
 #pragma unroll
-                for (int p = 0; p < NP; ++p) ts[p][threadIdx.x] = ay[p * H + i0 + threadIdx.x];
+                for (int p = 0; p < NP; ++p) ts[p][threadIdx.x] = di >= 0 && di < kc ? ay[p * H + i0 + di] : 0.0;
             }
             __syncthreads();
-            for (int ly = RW * wq; ly < RW * wq + RW - 1 + kc; ++ly) {
-                const double t0 = Ts[0][ly][lane];
-                const double t1 = Final ? 0.0 : Ts[1 % NP][ly][lane];
-                const double t2 = Final ? 0.0 : Ts[2 % NP][ly][lane];
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const int di = RW * wq + k + kc - 1 - ly;
-                    if (k < RW && di >= 0 && di < kc) {
-                        const double w0 = ts[0][di];
-                        acc[k][0] += w0 * t0;
-                        if (!Final) {
-                            acc[k][1 % NJ] += w0 * t1;
-                            acc[k][2 % NJ] += ts[1 % NP][di] * t0;
-                            acc[k][3 % NJ] += ts[2 % NP][di] * t0 + w0 * t2;
-                        }
-                    }
-                }
-            }
+            if (i0 + kYK < nr) fetch(i0 + kYK);
+            if (RW == 4) column_chunk<Final, 4>(Ts, ts, kc, wq, lane, acc);
+            else column_chunk<Final, 1>(Ts, ts, kc, wq, lane, acc);
         }
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
