@@ -14,17 +14,15 @@ namespace asp {
 namespace {
 
 // The packed keys (|v| bits << 32) | (0xFFFFFFFF - idx), one slot per
-// work-group index mod kPeakSlots: 512 bytes per GPU.
+// work-group index mod kPeakSlots: 512 bytes per GPU.  They are zero between
+// calls: the kernel that reads them clears them, which saves a launch (4096 x
+// 4096: 15.6 -> 14.0 us); calls that overlap, against the contract, still
+// leave them clear once the last has ended.
 __device__ __align__(256) unsigned long long scratch[kPeakSlots];
 
 constexpr int kMaxDevices = 64;
 std::mutex g_lock;
 unsigned long long *g_scratch[kMaxDevices];   // device address of `scratch` per GPU
-
-__global__ void k_na_clear(unsigned long long *slots)
-{
-    if (threadIdx.x < kPeakSlots) slots[threadIdx.x] = 0ull;
-}
 
 __global__ __launch_bounds__(256) void k_na_scan(const float *__restrict__ R, int64_t n,
                                                  unsigned long long *slots)
@@ -33,12 +31,12 @@ __global__ __launch_bounds__(256) void k_na_scan(const float *__restrict__ R, in
 }
 
 // One wave: the maximum over the slots, decoded into the pixel index and the
-// residual value there.
-__global__ void k_na_out(const float *__restrict__ R, const unsigned long long *slots,
+// residual value there (without a key, as in an image of NaN, there is none).
+__global__ void k_na_out(const float *__restrict__ R, unsigned long long *slots,
                          int64_t *idx_out, float *value_out)
 {
-    unsigned long long k = __hip_atomic_load(&slots[threadIdx.x], __ATOMIC_RELAXED,
-                                             __HIP_MEMORY_SCOPE_AGENT);
+    unsigned long long k = __hip_atomic_exchange(&slots[threadIdx.x], 0ull, __ATOMIC_RELAXED,
+                                                 __HIP_MEMORY_SCOPE_AGENT);
     for (int off = 32; off > 0; off >>= 1) {
         const unsigned long long o = __shfl_xor(k, off, 64);
         k = o > k ? o : k;
@@ -46,7 +44,7 @@ __global__ void k_na_out(const float *__restrict__ R, const unsigned long long *
     if (threadIdx.x == 0) {
         const int64_t idx = (int64_t)(0xFFFFFFFFu - (uint32_t)(k & 0xFFFFFFFFull));
         *idx_out = idx;
-        *value_out = R[idx];
+        *value_out = k ? R[idx] : __builtin_nanf("");
     }
 }
 
@@ -95,9 +93,7 @@ extern "C" asp_status asp_find_peak_noalloc(const float *R, int64_t H, int64_t W
     const int64_t need = (n / 4 + 255) / 256;
     const int64_t cap = 8 * (int64_t)cus;
     const int grid = (int)(need < 1 ? 1 : (need < cap ? need : cap));
-    hipLaunchKernelGGL(asp::k_na_clear, dim3(1), dim3(asp::kPeakSlots), 0, s, slots);
     hipLaunchKernelGGL(asp::k_na_scan, dim3(grid), dim3(256), 0, s, R, n, slots);
-    hipLaunchKernelGGL(asp::k_na_out, dim3(1), dim3(asp::kPeakSlots), 0, s, R,
-                       (const unsigned long long *)slots, idx_out, value_out);
+    hipLaunchKernelGGL(asp::k_na_out, dim3(1), dim3(asp::kPeakSlots), 0, s, R, slots, idx_out, value_out);
     return hipGetLastError() == hipSuccess ? ASP_OK : ASP_ERR_DEVICE;
 }
