@@ -982,7 +982,7 @@ __device__ __forceinline__ void evaluate_tiles_mfma(const Params &p, WGShared &S
 // five clocks each: a pixel's place is advanced from the last one's, its load
 // has no branch, a window's test selects the exponential alone, and a window
 // that no pixel of the wave lies in is left out.  Two members on eight
-// work-groups in a field of 1024 x 1024: 246 -> 208 us per trial.
+// work-groups in a field of 1024 x 1024: 246 -> 203 us per trial.
 template <int M>
 __device__ __forceinline__ void evaluate_tiles_reg(const Params &p, WGShared &S, int64_t tile0, int64_t stride,
                                    double *out, float *stage)
@@ -1784,7 +1784,7 @@ __device__ inline int eval_groups(int64_t ntiles, int nwg, int min_tiles)
 }
 
 // Up to this many parameters the leader sums all the rows of a shared trial
-// itself (reduce_flat): a row is at most 48 values, and the second level's
+// itself (sum_groups): a row is at most 48 values, and the second level's
 // hop between work-groups costs more than the reads.  Above, the last arrival
 // of a group sums the group's rows.
 constexpr int kFlatMaxN = 8;
