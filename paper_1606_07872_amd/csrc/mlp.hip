@@ -857,6 +857,7 @@ hipError_t forward_backward(asp_mlp *n, const float *x, const float *t, int64_t 
 // 2048, 56 for 3072, 71 for 4096.
 hipError_t forward(asp_mlp *n, const float *x, int64_t rows, float *y)
 {
+    if (rows == 0) return hipSuccess;      // a launch has no empty grid
     const float *w = n->w;
     if (rows <= n->bmax && rows <= kRowsByLayer) {
         const Op X = rows_of(x, (int)rows, kNetIn, nullptr, 0, nullptr);
