@@ -851,20 +851,40 @@ hipError_t forward_backward(asp_mlp *n, const float *x, const float *t, int64_t 
     return hipGetLastError();
 }
 
+// The forward pass layer by layer, at most bmax rows.  x has been read when y is
+// written.
+hipError_t forward_by_layer(asp_mlp *n, const float *x, int rows, float *y)
+{
+    const float *w = n->w;
+    const Op X = rows_of(x, rows, kNetIn, nullptr, 0, nullptr);
+    hidden(n, X);
+    hipLaunchKernelGGL(k_head<false>, dim3((unsigned)((rows + kHeadRows - 1) / kHeadRows)), dim3(256), 0,
+                       n->stream, n->H2, w + kOffW3, w + kOffB3, X, y, nullptr, nullptr);
+    return hipGetLastError();
+}
+
 // The forward pass of all rows.  A few rows leave most CUs idle in k_rows, whose
 // work-groups have all columns of a layer and take 54 us for up to 3072 rows;
 // layer by layer the columns are spread too: 38 us for up to 1024 rows, 47 for
-// 2048, 56 for 3072, 71 for 4096.
+// 2048, 56 for 3072, 71 for 4096.  k_rows writes the outputs of some rows while
+// it reads others, so outputs that lie within the inputs' memory (as a call may
+// have them that keeps the rows in place) are formed layer by layer too, bmax
+// rows at a time in order.
 hipError_t forward(asp_mlp *n, const float *x, int64_t rows, float *y)
 {
     if (rows == 0) return hipSuccess;      // a launch has no empty grid
     const float *w = n->w;
-    if (rows <= n->bmax && rows <= kRowsByLayer) {
-        const Op X = rows_of(x, (int)rows, kNetIn, nullptr, 0, nullptr);
-        hidden(n, X);
-        hipLaunchKernelGGL(k_head<false>, dim3((unsigned)((rows + kHeadRows - 1) / kHeadRows)), dim3(256), 0,
-                           n->stream, n->H2, w + kOffW3, w + kOffB3, X, y, nullptr, nullptr);
-        return hipGetLastError();
+    if (rows <= n->bmax && rows <= kRowsByLayer) return forward_by_layer(n, x, (int)rows, y);
+    const uintptr_t x0 = (uintptr_t)x, y0 = (uintptr_t)y;
+    const bool apart = y0 + sizeof(float) * kNetOut * (uintptr_t)rows <= x0 ||
+                       x0 + sizeof(float) * kNetIn * (uintptr_t)rows <= y0;
+    if (!apart) {
+        for (int64_t r = 0; r < rows; r += n->bmax) {
+            const int M = (int)(rows - r < n->bmax ? rows - r : n->bmax);
+            const hipError_t e = forward_by_layer(n, x + r * kNetIn, M, y + r * kNetOut);
+            if (e != hipSuccess) return e;
+        }
+        return hipSuccess;
     }
     const Net net{w, w + kOffB1, w + kOffW2, w + kOffB2, w + kOffW3, w + kOffB3};
     for (int64_t r = 0; r < rows; r += kRowsMax) {
