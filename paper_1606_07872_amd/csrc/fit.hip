@@ -1602,19 +1602,22 @@ __device__ __forceinline__ void lm_decide(const Params &p, WGShared &S, const do
     wave_lds_sync();
 }
 
-// The next point for n > 8, by the whole work-group after lm_decide.
+// The next point for n > 8, by the whole work-group after lm_decide.  Thread 0
+// writes S.finished only before the barrier at the loop's top (it wrote it last
+// itself), or behind the solve's barriers, so that every wave takes the same
+// way after it.
 __device__ __forceinline__ void lm_solve_large(const Params &p, WGShared &S, const double *H2, double *Lt)
 {
     const int t = threadIdx.x, n = __builtin_amdgcn_readfirstlane(S.n);
     const double *Hc = H2 + S.hsel * (kMaxN * kMaxN);
     for (;;) {
+        if (t == 0 && !S.finished) {
+            if (S.trials >= p.lm_max_iter) S.finished = 1;
+            else S.trials++;
+        }
         __syncthreads();
         if (S.finished) break;
         if (t < 64) {
-            if (t == 0) {
-                if (S.trials >= p.lm_max_iter) S.finished = 1;
-                else S.trials++;
-            }
             const double d = t < n ? Hc[t * n + t] : 0.0;
             const double dmax = wave_max0(d);
             if (t < n) {
@@ -1625,7 +1628,6 @@ __device__ __forceinline__ void lm_solve_large(const Params &p, WGShared &S, con
             }
         }
         __syncthreads();
-        if (S.finished) break;
         const double mu = S.mu;
         const bool ok = chol_solve(S, Hc, n, mu, Lt);
         if (ok) {
