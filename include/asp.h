@@ -238,13 +238,14 @@ asp_status asp_update_residual(asp_ctx *ctx, int64_t *pixels_touched);
  * search of asp_find_peak (the largest |R|, the lowest row-major index on
  * ties) over a caller's image, with no context and no allocation.
  *   R          device image H x W, row-major FP32, 16-byte aligned; read only.
- *   idx_out    device int64: the peak pixel r W + c.
- *   value_out  device float: R at that pixel.
+ *   idx_out    device int64: the peak pixel r W + c; 2^32 - 1 when every pixel
+ *              is NaN (a NaN has no magnitude to compare).
+ *   value_out  device float: R at that pixel; NaN without one.
  *   stream     the HIP stream (NULL: the null stream); the call is
  *              asynchronous and may be captured into a graph.
- * Its scratch (64 packed keys, 512 bytes) is a file-scope device array, one
- * copy per GPU, held until the process ends; the call clears it with a
- * kernel before every scan.  Calls that overlap on one GPU (other streams,
+ * Its scratch (256 packed keys, 2 KiB) is a file-scope device array, one
+ * copy per GPU, held until the process ends; a call reads only the keys that
+ * its own scan has written.  Calls that overlap on one GPU (other streams,
  * other threads) share that array and race.  Returns ASP_ERR_INVALID_ARG for
  * null pointers, H or W < 1, H W >= 2^32 - 1 (the maximum: the key holds a
  * 32-bit index) or an unaligned image, with a message on stderr for the

@@ -49,10 +49,11 @@ __device__ inline unsigned long long wave_max_u64(unsigned long long v)
     return v;
 }
 
-// The work-group's key goes to slots[rank % kPeakSlots] (a 64-bit atomicMax);
-// the peak is the maximum over the kPeakSlots slots.
-__device__ inline void peak_scan(const float *__restrict__ R, int64_t n, uint32_t rank,
-                                 uint32_t size, unsigned long long *slots)
+// The largest key of share `rank` of `size` work-groups, in every thread (0 where
+// no pixel of the share has a value that compares).  Work-groups of `Waves` waves.
+template <int Waves = 4>
+__device__ inline unsigned long long peak_key(const float *__restrict__ R, int64_t n, uint32_t rank,
+                                              uint32_t size)
 {
     const uint32_t n4 = (uint32_t)(n >> 2);
     const float4 *R4 = reinterpret_cast<const float4 *>(R);
@@ -78,16 +79,24 @@ __device__ inline void peak_scan(const float *__restrict__ R, int64_t n, uint32_
     if (bv >= 0.0f)
         key = ((unsigned long long)__float_as_uint(bv) << 32) | (unsigned long long)(0xFFFFFFFFu - bi);
     key = wave_max_u64(key);
-    __shared__ unsigned long long wk[4];
+    __shared__ unsigned long long wk[Waves];
     __syncthreads();
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     if (lane == 0) wk[wave] = key;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        unsigned long long k = wk[0];
-        for (int w = 1; w < (int)(blockDim.x >> 6); ++w) k = wk[w] > k ? wk[w] : k;
-        atomicMax(&slots[rank % kPeakSlots], k);
-    }
+    unsigned long long k = wk[0];
+#pragma unroll
+    for (int w = 1; w < Waves; ++w) k = wk[w] > k ? wk[w] : k;
+    return k;
+}
+
+// The work-group's key goes to slots[rank % kPeakSlots] (a 64-bit atomicMax);
+// the peak is the maximum over the kPeakSlots slots.
+__device__ inline void peak_scan(const float *__restrict__ R, int64_t n, uint32_t rank,
+                                 uint32_t size, unsigned long long *slots)
+{
+    const unsigned long long k = peak_key(R, n, rank, size);
+    if (threadIdx.x == 0) atomicMax(&slots[rank % kPeakSlots], k);
 }
 
 // ===========================================================================
