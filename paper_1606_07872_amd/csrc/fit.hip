@@ -2259,6 +2259,7 @@ __global__ __launch_bounds__(kT) void k_fit(Params p)
         __syncthreads();
         if (!S.stop) {
             const bool committed = fit_trials(p, G, S, tile, H2, nwg, 0);
+            if (!committed) flush_counts(p, S);
             // with fuse_update every work-group takes its tiles of the update
             // (Sect. 2 step 3) after this publication; the end of the kernel,
             // or the wait for every work-group, is the barrier before the next
@@ -2425,8 +2426,15 @@ __global__ __launch_bounds__(kT) void k_batch(BatchArgs b)
             collect_peak_key(P.st, true, &S.key);
             if (t == 0) fit_begin(P, S, false);
             __syncthreads();
-            if (S.stop) break;
-            if (!fit_trials(P, G, S, tile, H2, T, cur_field)) { ok = false; break; }
+            if (S.stop) {
+                flush_counts(P, S);                // the next field counts for itself
+                break;
+            }
+            if (!fit_trials(P, G, S, tile, H2, T, cur_field)) {
+                flush_counts(P, S);
+                ok = false;
+                break;
+            }
             // the residual update (Sect. 2 step 3)
             if (t == 0) {
                 const int32_t *bb = P.st->bb;
