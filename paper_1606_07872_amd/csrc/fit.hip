@@ -125,10 +125,16 @@ struct WGShared {
     // control
     unsigned long long tmark;      // phase timer mark (thread 0)
     unsigned long long tfit;       // start of the fit (thread 0)
+    unsigned long long tlaunch;    // start of the launch (thread 0)
     int32_t fresh;                 // the message opened a fit: th_old is new
     int32_t last, abort, solve, pd, ok, finished, accept, stop;
     int32_t upd;                   // the fit committed and this launch also updates R
+    int32_t more;                  // and another iteration follows it in this launch
 };
+
+// A launch of several iterations ends after the iteration that passes this
+// share of the wait limit of 2 s: 10 ms.
+constexpr unsigned long long kLaunchShare = 200;
 
 // Phase timers of the driving work-group (thread 0): the mark lives in LDS so
 // that no tick value stays in registers across a phase.
@@ -2202,6 +2208,7 @@ __global__ __launch_bounds__(kT) void k_fit(Params p)
         S.abort = spin_until(&G->top.n, (unsigned)nwg - 1u, p.spin_ticks) ? 0 : 1;
         st_shared(&G->top.n, 0u);
         lap(S, kPCheckin);
+        S.tlaunch = S.tmark;
     }
     __syncthreads();
     if (st->diag_m > 0) {
@@ -2254,7 +2261,7 @@ __global__ __launch_bounds__(kT) void k_fit(Params p)
         collect_peak_key(st, true, &S.key);
         if (t == 0) {
             fit_begin(p, S, S.abort != 0);
-            S.upd = 0;
+            S.upd = S.more = 0;
         }
         __syncthreads();
         if (!S.stop) {
@@ -2264,12 +2271,15 @@ __global__ __launch_bounds__(kT) void k_fit(Params p)
             // (Sect. 2 step 3) after this publication; the end of the kernel,
             // or the wait for every work-group, is the barrier before the next
             // iteration reads R
-            if (t == 0) S.upd = committed && p.fuse_update ? 1 : 0;
+            if (t == 0) {
+                S.upd = committed && p.fuse_update ? 1 : 0;
+                S.more = S.upd && it < p.iters && now_ticks() - S.tlaunch < p.spin_ticks / kLaunchShare ? 1 : 0;
+            }
         } else {
             flush_counts(p, S);
         }
         __syncthreads();
-        const bool upd = S.upd != 0, last = !upd || it >= p.iters;
+        const bool upd = S.upd != 0, last = S.more == 0;
         publish(G, S, upd ? kCmdUpdate : kCmdExit, last ? 1 : 0, upd);
         if (upd) update_tiles(p, 0, nwg, tile);
         if (last) return;
