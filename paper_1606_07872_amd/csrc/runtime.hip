@@ -632,8 +632,17 @@ asp_status enqueue_refresh(asp_ctx *c, int force)
 // queues launches for up to 256 iterations and goes on from what they did.
 constexpr int64_t kRunIters = 32;
 
+// The search inside the kernel has one work-group per CU and reads the whole
+// image more slowly than the search's own launch with eight.  Per iteration, a
+// launch for 32 against a launch per step: 59 and 79 us at 1024 x 1024, 102 and
+// 115 at 8192^2, 245 and 259 at 16384^2, 353 and 359 at 20480^2, 482 and 490 at
+// 24576^2, but 820 and 787 at 32768^2.  The incremental search (97 and 112 there)
+// has no such bound.
+constexpr int64_t kRunScanPixels = (int64_t)1 << 29;
+
 bool runs_whole(const asp_ctx *c)
 {
+    if (!c->pk_tiles && c->H * c->W > kRunScanPixels) return false;
     return c->opt.refresh_every <= 0 && c->opt.update_launch == 0 && c->opt.init_mode != 1 &&
            !c->P.smooth && c->P.rec_cap == 0 && !c->timing;
 }
