@@ -234,11 +234,6 @@ __host__ __device__ inline void make_window(double x, double y, int h, int64_t H
     box[3] = (int32_t)(c1 > W - 1 ? W - 1 : c1);
 }
 
-__host__ __device__ inline bool in_box(const int32_t b[4], int32_t r, int32_t c)
-{
-    return r >= b[0] && r <= b[1] && c >= b[2] && c <= b[3];
-}
-
 __device__ inline double width_cap(const Params &p)
 {
     double m = p.max_width > 0.0 ? p.max_width

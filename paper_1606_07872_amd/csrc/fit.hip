@@ -677,8 +677,8 @@ __device__ inline double wave_sum(double v)
     return v;
 }
 
-// in_box without branches between the comparisons (each would wait for its own
-// LDS read).
+// Whether pixel (r, c) lies in the window, without branches between the
+// comparisons (each would wait for its own LDS read).
 __device__ __forceinline__ bool inside(const int32_t b[4], int32_t r, int32_t c)
 {
     return (r >= b[0]) & (r <= b[1]) & (c >= b[2]) & (c <= b[3]);
@@ -1244,14 +1244,6 @@ __device__ __forceinline__ void put_sum(WGShared &S, double *He, int n, int o, d
     out_pair(o, n, i, k);
     if (i < n && k < n) { He[i * n + k] = v; He[k * n + i] = v; }
     else if (i < n) S.ge[i] = v;
-}
-
-// Rows w0..w1-1 of the partials summed in row order into He, S.ge, S.Fe, ...
-__device__ __forceinline__ void reduce_partials(const Params &p, WGShared &S, int w0, int w1, double *He)
-{
-    const int n = S.n, nv = (n + 1) * (n + 2) / 2 + 3;
-    for (int o = threadIdx.x; o < nv; o += kT) put_sum(S, He, n, o, sum_column(p, w0, w1, o));
-    __syncthreads();
 }
 
 // ---------------------------------------------------------------------------
@@ -2298,8 +2290,12 @@ __global__ __launch_bounds__(kT) void k_fit(Params p)
 // first, and runs each field's minor cycle for up to n_iter iterations:
 // rank 0 leads as work-group 0 of k_fit does and the others follow its
 // commands -- a share of the peak search, a share of an LM trial, a share of
-// the residual update, or exit.  Every command is acknowledged by every member
-// before the next one is published; every wait is bounded.
+// the residual update, or exit.  A share of the search or of the update is
+// acknowledged by every member before the next command, a trial only by the
+// members with tiles of it: the others may find that the leader has moved on and
+// never read that message.  What an unread message could have told of R or of
+// the update's plan is in every message: the epoch, whose change makes a member
+// acquire before it reads them again.  Every wait is bounded.
 // ===========================================================================
 
 // The field's parameters with the team's exchange buffers and the batch's

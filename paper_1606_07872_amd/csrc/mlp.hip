@@ -23,8 +23,6 @@
 //   * the trainer object of the C ABI (asp_mlp_*).
 // The training loss is the mean over samples and outputs of (y - t)^2.
 #include <math.h>
-
-#include <type_traits>
 #include <string.h>
 
 #include <string>
