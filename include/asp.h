@@ -290,6 +290,10 @@ asp_status asp_step(asp_ctx *ctx);
  * With update_launch 0 (the default) the residual update is done by the fit
  * kernel's work-groups after the commit, in the same launch; with 1 it is a
  * launch of its own.  The residual is the same bit for bit either way.
+ * Where an iteration is nothing but the peak search, the fit and the update (no
+ * network, smoothing, recording, refresh or kernel timing, update_launch 0, a
+ * searched image of at most 2^29 pixels), up to 32 of them share a launch, which
+ * ends after the one that passes 10 ms; the results are those of asp_step.
  * Returns ASP_OK (n_iter done), ASP_STOP_THRESHOLD or ASP_STOP_MAXITER.
  * rep may be NULL.
  */

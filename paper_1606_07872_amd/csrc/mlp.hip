@@ -589,7 +589,7 @@ __global__ __launch_bounds__(256) void k_back1(Op X, const float *dH1, float *dw
 // 32 w .. 32 w + 31 of a layer, RT x 2 tiles of 16 x 16.  The weights (1.3 MB,
 // from L2, once per kRT tiles) and X stream through LDS kFC values of k at a
 // time, two buffers and kFAhead chunks on their way.  The bound is the matrix
-// cores at 256 FP32 flops a clock and CU: 50000 rows take 370 us, 58 % of that
+// cores at 256 FP32 flops a clock and CU: 50000 rows take 350 us, 61 % of that
 // rate (layer by layer with 512 rows a launch they took 25 ms).  32 rows a
 // work-group, two work-groups a CU, took 405 us: twice the reads of the weights.
 constexpr int kFC = 16, kFAhead = 4, kFStride = kFC + 4, kHStride = kNetH + 4, kRT = 4;
