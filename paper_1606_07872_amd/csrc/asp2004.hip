@@ -460,8 +460,9 @@ __device__ __forceinline__ void column_chunk(const double (*Ts)[kYR + kYK - 1][k
 // leave work-groups idle (small images).  Per chunk of row taps the
 // work-group stages the rows of T it reaches in LDS, while the next chunk's are
 // on their way, then wave w accumulates output rows RW w .. RW w + RW - 1 of its
-// lane's column.  Bound by the FP64 FMAs of one wave per SIMD: at 512 x 512 25 us
-// an evaluation, 36 with a test per row and tap and a plane loaded at a time.
+// lane's column.  Bound by the FP64 FMAs of one wave per SIMD: at 512 x 512 31 us
+// an evaluation; 24 a launch with those behind a fit's end, where a test per row
+// and tap and a plane loaded at a time took 36.
 // Then per pixel the
 // sums of k_a4_gram, reduced in the same fixed order into partial row b; or,
 // for the update, R -= gain F B(*)g.
