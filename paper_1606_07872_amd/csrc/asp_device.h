@@ -188,7 +188,7 @@ struct Params {
     int32_t *rec_flag;             // rec_cap: 1 converged fit from the simple values
     int64_t rec_cap;
     int32_t smooth;                // the smoothing method and its switch are on
-    int32_t iters;                 // > 0: k_fit runs this many iterations, the peak search included
+    int32_t iters;                 // > 0: k_fit runs up to this many iterations, the peak search included
     SmoothParams sm;
 };
 
